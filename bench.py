@@ -43,7 +43,7 @@ METRIC = "fused keyframe-update Mpixel/s at 640x480 + p50/p99 fuse latency"
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "solver_640x480_traffic.json")
 BATCH_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "solver_batched64_traffic.json")
-SOLVER_SRCS = tuple(os.path.join(ROOT, "paper_2207_12244_amd", "csrc", f) for f in ("kf_solve.hip", "kf_internal.h"))
+SOLVER_SRCS = tuple(os.path.join(ROOT, "paper_2207_12244_amd", "csrc", f) for f in ("kf_solve.hip", "kf_sstep.h", "kf_device.h", "kf_internal.h"))
 
 WORKLOAD = dict(config=2, W=640, H=480, frames=30, precision="bf16", pattern="sq5x5", n_samples=128,
                 n_gn=10, n_cg=20)

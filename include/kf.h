@@ -102,9 +102,11 @@ typedef struct {
   int32_t n_cg;                 /* PCG iterations per GN iteration when cg_rtol == 0, >= 1 */
   double cg_rtol;               /* > 0: PCG until ||r|| <= cg_rtol ||b||, at most cg_max */
   int32_t cg_max;               /* cap of the tolerance mode, >= 1 */
-  int32_t cg_variant;           /* 0 automatic (pipelined when cg_rtol == 0), 1 textbook PCG,
-                                   2 pipelined PCG: same iterates in exact arithmetic, one team
-                                   synchronisation per iteration instead of two */
+  int32_t cg_variant;           /* 0 automatic: with cg_rtol == 0 pipelined, and in the float
+                                   precisions with solver_threads 0 s-step PCG; 1 textbook PCG;
+                                   2 pipelined PCG. Same iterates in exact arithmetic; one team
+                                   synchronisation per iteration (pipelined) or per 2 or 4 (s-step)
+                                   instead of two */
   double huber_delta;           /* threshold c of the robust cost on whitened residuals (> 0; INFINITY
                                    gives plain least squares with Huber) */
   double d_near, d_far;         /* depth range of a full-line search, 0 < d_near < d_far */
@@ -244,11 +246,12 @@ kf_status kf_read_depth(kf_ctx* ctx, void* depth_out, void* var_out, double* sca
    capture, serving loops and harnesses that forbid allocation): kf_fuse_frame
    with the same results, whose kernels take their scratch -- the staged new
    frame and the solver team's exchange words -- from a fixed array inside the
-   library (4 MiB per device, held until the process ends) instead of the
+   library (24 MiB per device, held until the process ends) instead of the
    context's workspace. Allocates nothing and calls no allocating routine.
-   KF_ERR_ARG if the keyframe needs more scratch than the array holds
-   ((height + 1) x row stride of the staged frame, rows padded to a multiple of
-   64 bytes >= width + 8, plus the exchange words: 640 x 480 needs 2.8 MB);
+   KF_ERR_ARG if the keyframe needs more than 4 MiB of scratch, counted with the
+   exchange words of pipelined PCG ((height + 1) x row stride of the staged
+   frame, rows padded to a multiple of 64 bytes >= width + 8, plus those words:
+   640 x 480 needs 2.8 MB); the array holds what s-step PCG takes beyond that;
    KF_ERR_STATE before kf_set_prior or with pipeline_frames. Every call on a
    device shares that device's array and clears what must start at zero, so
    calls that overlap on one device (contexts on different streams) race. */

@@ -1,5 +1,6 @@
 // C ABI of the keyframe depth-update library: validation, workspace layout,
 // per-frame epipolar constants (host FP64) and kernel launches.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -87,6 +88,8 @@ bool tiling_ok(int W, int H, int tx, int ty, int threads, int prec, Tiling* t) {
   t->blocks = tx * ty;
   t->ppt = ppt;
   t->threads = threads;
+  t->s = t->rows = t->cells = 0;
+  t->base_threads = threads;
   return true;
 }
 
@@ -103,7 +106,7 @@ double iteration_us(const Tiling& c) {
 }
 
 // Picks the tile grid (and workgroup size, unless given) minimising iteration_us.
-bool choose_tiling(int W, int H, int tx_req, int ty_req, int threads_req, int prec, Tiling* t) {
+bool choose_tiling_classic(int W, int H, int tx_req, int ty_req, int threads_req, int prec, Tiling* t) {
   const int thr_opts[3] = {512, 256, 1024};
   if (tx_req > 0 && ty_req > 0) {
     for (int nt : thr_opts) {
@@ -137,6 +140,129 @@ bool choose_tiling(int W, int H, int tx_req, int ty_req, int threads_req, int pr
 
 int stage_stride(int W) { return stage_stride_impl(W); }
 
+namespace {
+
+constexpr int SS_THREADS = 512;
+constexpr size_t SS_SMEM_MAX = 150 * 1024;   // of 160 KiB; the kernels add up to 10 KB of their own
+
+// Whether a tile grid fits the s-step solver with `rows` pixels per thread; the
+// extended tile (the ghost frame included) is laid out column by row group over
+// the threads, and a ghost frame never reaches past the adjacent tile.
+bool sstep_fit(int W, int H, int tx, int ty, int s, int rows, Tiling* t) {
+  if (tx < 1 || ty < 1 || tx > W || ty > H || tx * ty > MAX_TEAM) return false;
+  const int tw = (W + tx - 1) / tx, th = (H + ty - 1) / ty;
+  if ((tx - 1) * tw >= W || (ty - 1) * th >= H) return false;
+  if ((tx > 1 && tw < s + 1) || (ty > 1 && th < s + 1)) return false;
+  const int ew = std::min(W, tw + s * std::min(2, tx - 1)), eh = std::min(H, th + s * std::min(2, ty - 1));
+  const int groups = (eh + rows - 1) / rows;
+  if (ew * groups > SS_THREADS || 2 * (ew + eh) > SS_THREADS) return false;
+  if ((size_t)tx * ty * sstep_frame_words(tw, th, s) >= (1u << 24)) return false;
+  t->tiles_x = tx;
+  t->tiles_y = ty;
+  t->tile_w = tw;
+  t->tile_h = th;
+  t->blocks = tx * ty;
+  t->threads = SS_THREADS;
+  t->ppt = (tw * th + SS_THREADS - 1) / SS_THREADS;
+  t->s = s;
+  t->rows = rows;
+  t->cells = (ew + 2) * (groups * rows + 2);
+  return sstep_smem_bytes(*t) <= SS_SMEM_MAX;
+}
+
+}  // namespace
+
+// Latency model of the s-step solver, microseconds per Gauss-Newton iteration:
+// its blocks and its scale step, each one synchronisation. Fitted to 330 solves
+// of 32 x 24 to 640 x 480 px (10 x 20 iterations) over tile grids, s and rows; rms 4 %
+// (s = 4, rows = 4: 280 us measured on 100 tiles of 7 x 5, 342 us on 240 tiles of
+// 40 x 32; s = 2, rows = 12: 439 us on one tile, 756 us on 4 of 80 x 60). The
+// pixel data of a tile's frame and the lines of the team's members cost as shown.
+double sstep_gn_us(const Tiling& t, int n_cg) {
+  const double edge = t.tile_w + t.tile_h, team = t.blocks / 256.0;
+  double us;
+  if (t.s == 4)
+    us = t.blocks == 1 ? 2.0 + 0.32 * t.rows : 2.6 + 0.42 * t.rows + 0.011 * edge + 0.7 * team;
+  else
+    us = (t.blocks == 1 ? 0.8 : 1.9 + 0.0045 * edge + 0.5 * team) +
+         (t.rows <= 6 ? 0.28 : 0.32) * t.rows + (t.rows > 12 ? 0.8 : 0.0);   // 14 rows spill
+  return ((n_cg + t.s - 1) / t.s + 1) * us;
+}
+
+namespace {
+
+// The best (s, rows) for one tile grid; false if none fits.
+bool sstep_grid(int W, int H, int tx, int ty, int n_cg, Tiling* t) {
+  double best = 1e300;
+  auto offer = [&](int s, int rows) {
+    Tiling c{};
+    if (!sstep_fit(W, H, tx, ty, s, rows, &c)) return;
+    const double cost = sstep_gn_us(c, n_cg);
+    if (cost < best) {
+      best = cost;
+      *t = c;
+    }
+  };
+#define KF_OFFER2(R) offer(2, R);
+#define KF_OFFER4(R) offer(4, R);
+  KF_SS2_ROWS(KF_OFFER2)
+  KF_SS4_ROWS(KF_OFFER4)
+#undef KF_OFFER2
+#undef KF_OFFER4
+  return best < 1e300;
+}
+
+// Configurations whose depth steps the s-step solver makes: the automatic CG
+// variant with a fixed count in the float precisions, with pairwise terms. An
+// explicit workgroup size asks for kf_solve.hip, whose kernels have that choice
+// (and whose results, to the last bit, such a configuration has always had).
+bool sstep_applies(const kf_config& c) {
+  return c.precision != KF_F64 && c.cg_rtol == 0.0 && c.cg_variant == 0 && c.variant != KF_VARIANT_NO_PAIRWISE &&
+         c.solver_threads == 0 && solve_epoch_bound(c) < 30000;
+}
+
+}  // namespace
+
+bool choose_tiling(const kf_config& c, Tiling* t) {
+  const int W = c.width, H = c.height;
+  if (!choose_tiling_classic(W, H, c.solver_tiles_x, c.solver_tiles_y, c.solver_threads, c.precision, t)) return false;
+  if (!sstep_applies(c)) return true;
+  const int base = t->threads;
+  if (c.solver_tiles_x > 0) {
+    Tiling f{};
+    if (sstep_grid(W, H, c.solver_tiles_x, c.solver_tiles_y, c.n_cg, &f)) *t = f;
+    t->base_threads = base;
+    return true;
+  }
+  double best = 1e300;
+  for (int tx = 1; tx <= 64 && tx <= W; ++tx)
+    for (int ty = 1; ty <= 64 && ty <= H && tx * ty <= MAX_TEAM; ++ty) {
+      Tiling f{};
+      if (!sstep_grid(W, H, tx, ty, c.n_cg, &f)) continue;
+      const double cost = sstep_gn_us(f, c.n_cg);
+      if (cost < best) {
+        best = cost;
+        *t = f;
+      }
+    }
+  t->base_threads = base;
+  return true;
+}
+
+// Partial-sum words: [2 parities][NV_MAX][PART_REPLICAS][blocks] of two words
+// (the s-step solver's [2][blocks] lines of 16 words fit too).
+size_t partial_words_bytes(const Tiling& t) {
+  return align256((size_t)2 * NV_MAX * PART_REPLICAS * t.blocks * 2 * 8);
+}
+
+// Boundary words: of kf_solve.hip's exchange (also the synchronisation probe's),
+// or of the s-step solver's where that is more.
+size_t exchange_words_bytes(const Tiling& t) {
+  const size_t classic = (size_t)2 * t.blocks * 2 * (2 * t.tile_w + 2 * t.tile_h) * 2 * 8;
+  const size_t sstep = t.s ? (size_t)2 * t.s * t.blocks * sstep_frame_words(t.tile_w, t.tile_h, t.s) * 4 : 0;
+  return align256(std::max(classic, sstep));
+}
+
 bool layout_for(const kf_config& c, const Tiling& t, Layout* L) {
   const size_t N = (size_t)c.width * c.height;
   const size_t elt = c.precision == KF_F64 ? 8 : 4;
@@ -158,8 +284,8 @@ bool layout_for(const kf_config& c, const Tiling& t, Layout* L) {
   L->match = off; off += align256(N * 4);
   L->i1s = off; off += align256((size_t)(c.height + 1) * stage_stride(c.width));
   L->scal = off; off += 256;
-  L->parts = off; off += align256((size_t)2 * NV_MAX * PART_REPLICAS * t.blocks * 2 * 8);
-  L->halo = off; off += align256((size_t)2 * t.blocks * 2 * (2 * t.tile_w + 2 * t.tile_h) * 2 * 8);
+  L->parts = off; off += partial_words_bytes(t);
+  L->halo = off; off += exchange_words_bytes(t);
   L->total = off;
   return true;
 }
@@ -340,6 +466,9 @@ void solve_args(kf_ctx* c, SolveArgs* a) {
   a->scal = scal_ptr(c);
   a->parts = ws_ptr<uint64_t>(c, c->lay.parts);
   a->halo = ws_ptr<uint64_t>(c, c->lay.halo);
+  a->s = c->tiling.s;
+  a->rows = c->tiling.rows;
+  a->cells = c->tiling.cells;
   a->perim = 2 * c->tiling.tile_w + 2 * c->tiling.tile_h;
   // the second-ring cells (perimeter + 4 corners) fit one slot per thread
   a->ghost_z = (solve_pipelined(g) && g.cg_rtol == 0.0 && c->tiling.tile_w >= 2 && c->tiling.tile_h >= 2 &&
@@ -378,8 +507,21 @@ namespace {
 // exchange words live here instead of the context's workspace. Each device
 // holds its own copy for the life of the process; host code uses only the
 // per-device address that hipGetSymbolAddress returns, never the symbol.
-constexpr size_t KF_STATIC_SCRATCH_BYTES = (size_t)4 << 20;
+// Which keyframes it takes is decided on the staged frame and kf_solve.hip's
+// exchange words (static_need, at most KF_STATIC_LIMIT_BYTES). The s-step
+// solver's words of every such keyframe fit the array: at most 256 tiles with
+// tile_w + tile_h <= 248 (sstep_fit) take 2 * 4 * 256 * 10 * 248 * 4 bytes of pixel
+// data (19.4 MiB) and 0.2 MiB of lines, beside at most 4 MiB of staged frame.
+constexpr size_t KF_STATIC_LIMIT_BYTES = (size_t)4 << 20;
+constexpr size_t KF_STATIC_SCRATCH_BYTES = (size_t)24 << 20;
 static __device__ __align__(256) unsigned char scratch[KF_STATIC_SCRATCH_BYTES];
+
+size_t static_need(const kf_config& g) {
+  Tiling t{};
+  if (!choose_tiling_classic(g.width, g.height, g.solver_tiles_x, g.solver_tiles_y, g.solver_threads, g.precision, &t))
+    return SIZE_MAX;
+  return align256((size_t)(g.height + 1) * stage_stride(g.width)) + partial_words_bytes(t) + exchange_words_bytes(t);
+}
 
 constexpr int KF_MAX_DEVICES = 64;
 std::mutex g_scratch_mu;
@@ -448,7 +590,7 @@ void kf_config_default(kf_config* cfg, int32_t width, int32_t height) {
 size_t kf_workspace_bytes(const kf_config* cfg) {
   if (!cfg || validate(*cfg)) return 0;
   Tiling t;
-  if (!choose_tiling(cfg->width, cfg->height, cfg->solver_tiles_x, cfg->solver_tiles_y, cfg->solver_threads, cfg->precision, &t)) return 0;
+  if (!choose_tiling(*cfg, &t)) return 0;
   Layout L;
   layout_for(*cfg, t, &L);
   return L.total;
@@ -460,7 +602,7 @@ kf_status kf_create(const kf_config* cfg, kf_ctx** out) {
   if (!cfg) return KF_ERR_ARG;
   if (validate(*cfg)) return KF_ERR_ARG;
   Tiling t;
-  if (!choose_tiling(cfg->width, cfg->height, cfg->solver_tiles_x, cfg->solver_tiles_y, cfg->solver_threads, cfg->precision, &t)) return KF_ERR_ARG;
+  if (!choose_tiling(*cfg, &t)) return KF_ERR_ARG;
   Layout L;
   layout_for(*cfg, t, &L);
   if (!cfg->workspace) return KF_ERR_ARG;
@@ -745,10 +887,11 @@ kf_status kf_fuse_frame_static(kf_ctx* c, const uint8_t* image1, const double T_
   if (!pose_ok(T_wc1)) return fail(c, KF_ERR_ARG, "kf_fuse_frame_static: pose must be finite with last row 0 0 0 1");
   const size_t stage = align256((size_t)(c->cfg.height + 1) * stage_stride(c->cfg.width));
   const size_t exch = c->lay.total - c->lay.parts;   // exchange words of the solver team
-  if (stage + exch > KF_STATIC_SCRATCH_BYTES)
-    return fail(c, KF_ERR_ARG, "kf_fuse_frame_static: this keyframe needs " + std::to_string(stage + exch) +
+  const size_t need = static_need(c->cfg);
+  if (need > KF_STATIC_LIMIT_BYTES || stage + exch > KF_STATIC_SCRATCH_BYTES)
+    return fail(c, KF_ERR_ARG, "kf_fuse_frame_static: this keyframe needs " + std::to_string(need) +
                                    " bytes of scratch, the static array holds " +
-                                   std::to_string(KF_STATIC_SCRATCH_BYTES));
+                                   std::to_string(KF_STATIC_LIMIT_BYTES));
   char* base = nullptr;
   hipError_t e = static_scratch(c->device, &base);
   if (e != hipSuccess) return hip_fail(c, e, "kf_fuse_frame_static (static scratch address)");

@@ -21,21 +21,40 @@ namespace {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+// Solver launches of a batch, by the kernel family that its members' tilings
+// take: kf_solve.hip's, or the s-step solver's. A batch of one family makes
+// one launch.
+constexpr int FAMILIES = 2;
+int family_of(const Tiling& t) { return t.s ? 1 : 0; }
+
 // Per-call region of the batch workspace (uploaded as a whole).
 struct DynLayout {
-  size_t hdr, st, queue, qoff, total;
+  size_t hdr, st, queue[FAMILIES], qoff[FAMILIES], total;
 };
 
-DynLayout dyn_layout(int n, int members_total) {
+DynLayout dyn_layout(kf_ctx* const* m, int n) {
+  int blocks[FAMILIES] = {};
+  for (int i = 0; i < n; ++i) blocks[family_of(m[i]->tiling)] += m[i]->tiling.blocks;
   DynLayout L;
   size_t off = 0;
   L.hdr = off; off += 256;
   L.st = off; off += align256((size_t)n * sizeof(StereoArgs));
-  L.queue = off; off += align256((size_t)members_total * 4);
-  L.qoff = off; off += align256((size_t)(members_total + 1) * 4);
+  for (int f = 0; f < FAMILIES; ++f) {
+    L.queue[f] = off; off += align256((size_t)blocks[f] * 4);
+    L.qoff[f] = off; off += blocks[f] ? align256((size_t)(blocks[f] + 1) * 4) : 0;
+  }
   L.total = off;
   return L;
 }
+
+// One family's launch.
+struct Family {
+  SolveKernel k{};
+  size_t smem = 0;
+  int grid = 0;                    // workgroups; 0: no member of this family
+  int max_queue = 0;               // longest per-workgroup queue of the last schedule
+  std::vector<int32_t> queue, qoff;
+};
 
 }  // namespace
 
@@ -45,12 +64,7 @@ struct kf_batch {
   hipStream_t capture = nullptr;   // private stream the graphs are captured on
   int device = 0;
   int prec = 0, pattern = 0, ns = 0, threads = 0, ppt = 0;
-  bool pipelined = false;
-  int kind = 0;                 // solve_kind of the launch: pipelined bit | any member's variant bit
-  size_t smem = 0;
-  int grid = 0;                    // solver workgroups
-  int max_queue = 0;               // longest per-workgroup queue of the last schedule
-  int capacity = 0;                // co-resident workgroups of the batched solver
+  Family fam[FAMILIES];
   int cus = 256;   // compute units of the device (stereo grid)
   bool use_graph = true;
   DynLayout dl{};
@@ -62,7 +76,6 @@ struct kf_batch {
   int parity = 0;
   // captured launch sequences: 0 = stereo + solve, 1 = stereo, 2 = solve
   hipGraphExec_t exec[3] = {nullptr, nullptr, nullptr};
-  std::vector<int32_t> queue, qoff;
   std::string err;
 
   ~kf_batch() {
@@ -80,8 +93,8 @@ struct kf_batch {
 
   const int32_t* d_n() const { return reinterpret_cast<const int32_t*>(d_dyn + dl.hdr); }
   const StereoArgs* d_st() const { return reinterpret_cast<const StereoArgs*>(d_dyn + dl.st); }
-  const int32_t* d_queue() const { return reinterpret_cast<const int32_t*>(d_dyn + dl.queue); }
-  const int32_t* d_qoff() const { return reinterpret_cast<const int32_t*>(d_dyn + dl.qoff); }
+  const int32_t* d_queue(int f) const { return reinterpret_cast<const int32_t*>(d_dyn + dl.queue[f]); }
+  const int32_t* d_qoff(int f) const { return reinterpret_cast<const int32_t*>(d_dyn + dl.qoff[f]); }
 };
 
 namespace {
@@ -95,18 +108,13 @@ kf_status bhip(kf_batch* b, hipError_t e, const std::string& where) {
   return bfail(b, KF_ERR_HIP, where + ": " + hipGetErrorString(e));
 }
 
-int total_members(kf_ctx* const* m, int n) {
-  int s = 0;
-  for (int i = 0; i < n; ++i) s += m[i]->tiling.blocks;
-  return s;
-}
-
 size_t static_bytes(int n) { return align256((size_t)n * sizeof(SolveArgs)); }
 
 // Estimated duration of one keyframe's solve (microseconds): the latency
-// model of the single-keyframe tiling choice times the synchronisations.
+// models of the single-keyframe tiling choice.
 double team_cost(const kf_ctx* c) {
   const kf_config& g = c->cfg;
+  if (c->tiling.s) return g.n_gn * sstep_gn_us(c->tiling, g.n_cg);
   const double cg = g.cg_rtol > 0.0 ? (double)g.cg_max : (double)g.n_cg;
   return g.n_gn * (cg + 2.0) * iteration_us(c->tiling);
 }
@@ -122,13 +130,17 @@ double team_cost(const kf_ctx* c) {
 // against 1.17 with the teams placed in order of decreasing cost (measured:
 // 7.4 against 8.3 ms per batched solve). Every workgroup's queue follows the
 // one global team order, which keeps the launch free of deadlock.
-void schedule(kf_batch* b, const std::vector<int>& active) {
+void schedule(kf_batch* b, int f, const std::vector<int>& members) {
+  Family& fam = b->fam[f];
+  std::vector<int> active;
+  for (int c : members)
+    if (family_of(b->m[c]->tiling) == f) active.push_back(c);
   std::vector<double> cost(b->m.size(), 0.0);
   for (int c : active) cost[c] = team_cost(b->m[c]);
-  std::vector<double> avail(b->grid, 0.0);
-  std::vector<std::vector<int32_t>> q(b->grid);
-  std::vector<int> idx(b->grid);
-  std::vector<double> sorted_avail(b->grid);
+  std::vector<double> avail(fam.grid, 0.0);
+  std::vector<std::vector<int32_t>> q(fam.grid);
+  std::vector<int> idx(fam.grid);
+  std::vector<double> sorted_avail(fam.grid);
   std::vector<int> rest(active);
   while (!rest.empty()) {
     sorted_avail = avail;
@@ -143,7 +155,7 @@ void schedule(kf_batch* b, const std::vector<int>& active) {
     const int c = rest[pick];
     rest.erase(rest.begin() + (std::ptrdiff_t)pick);
     const int B = b->m[c]->tiling.blocks;
-    for (int g = 0; g < b->grid; ++g) idx[g] = g;
+    for (int g = 0; g < fam.grid; ++g) idx[g] = g;
     std::partial_sort(idx.begin(), idx.begin() + B, idx.end(), [&](int x, int y) {
       return avail[x] < avail[y] || (avail[x] == avail[y] && x < y);
     });
@@ -155,13 +167,13 @@ void schedule(kf_batch* b, const std::vector<int>& active) {
       q[idx[k]].push_back((int32_t)((c << 8) | k));
     }
   }
-  b->queue.clear();
-  b->qoff.assign(1, 0);
-  b->max_queue = 0;
-  for (int g = 0; g < b->grid; ++g) {
-    b->queue.insert(b->queue.end(), q[g].begin(), q[g].end());
-    b->qoff.push_back((int32_t)b->queue.size());
-    b->max_queue = std::max(b->max_queue, (int)q[g].size());
+  fam.queue.clear();
+  fam.qoff.assign(1, 0);
+  fam.max_queue = 0;
+  for (int g = 0; g < fam.grid; ++g) {
+    fam.queue.insert(fam.queue.end(), q[g].begin(), q[g].end());
+    fam.qoff.push_back((int32_t)fam.queue.size());
+    fam.max_queue = std::max(fam.max_queue, (int)q[g].size());
   }
 }
 
@@ -169,9 +181,9 @@ hipError_t enqueue(kf_batch* b, int which, hipStream_t s) {
   hipError_t e = hipSuccess;
   if (which != 2)
     e = launch_stereo_batch(b->prec, b->pattern, b->ns, b->d_st(), b->d_n(), (int)b->m.size(), b->cus, s);
-  if (e == hipSuccess && which != 1)
-    e = launch_solve_batch(b->prec, b->threads, b->ppt, b->kind, b->d_so, b->d_queue(), b->d_qoff(), b->grid,
-                           b->smem, s);
+  for (int f = 0; f < FAMILIES && e == hipSuccess && which != 1; ++f)
+    if (b->fam[f].grid)
+      e = launch_solve_batch(b->fam[f].k, b->d_so, b->d_queue(f), b->d_qoff(f), b->fam[f].grid, b->fam[f].smem, s);
   return e;
 }
 
@@ -224,16 +236,22 @@ kf_status run_call(kf_batch* b, int which, const std::vector<int>& active, const
     for (size_t k = 0; k < active.size(); ++k)
       if (!stereo_args(b->m[active[k]], images[k], poses + 16 * k, &hst[k]))
         return bfail(b, KF_ERR_ARG, std::string(who) + ": singular pose for member " + std::to_string(active[k]));
+  for (int f = 0; f < FAMILIES; ++f) {
+    Family& fam = b->fam[f];
+    if (!fam.grid) continue;
+    if (solve) {
+      schedule(b, f, active);
+      std::memcpy(h + b->dl.queue[f], fam.queue.data(), fam.queue.size() * 4);
+      std::memcpy(h + b->dl.qoff[f], fam.qoff.data(), fam.qoff.size() * 4);
+    } else {
+      std::memset(h + b->dl.qoff[f], 0, (size_t)(fam.grid + 1) * 4);
+    }
+  }
   if (solve) {
-    schedule(b, active);
-    std::memcpy(h + b->dl.queue, b->queue.data(), b->queue.size() * 4);
-    std::memcpy(h + b->dl.qoff, b->qoff.data(), b->qoff.size() * 4);
     for (int i : active) {
       e = epoch_wrap_if_needed(b->m[i], solve_epoch_bound(b->m[i]->cfg));
       if (e != hipSuccess) return bhip(b, e, std::string(who) + " (epoch wrap)");
     }
-  } else {
-    std::memset(h + b->dl.qoff, 0, (size_t)(b->grid + 1) * 4);
   }
   e = hipMemcpyAsync(b->d_dyn, h, b->dl.total, hipMemcpyHostToDevice, b->stream);
   if (e == hipSuccess) e = hipEventRecord(b->ev[p], b->stream);
@@ -274,7 +292,7 @@ size_t kf_batch_workspace_bytes(kf_ctx* const* members, int32_t n) {
   if (!members || n < 1 || n > KF_BATCH_MAX) return 0;
   for (int i = 0; i < n; ++i)
     if (!members[i]) return 0;
-  return static_bytes(n) + dyn_layout(n, total_members(members, n)).total;
+  return static_bytes(n) + dyn_layout(members, n).total;
 }
 
 kf_status kf_batch_create(kf_ctx* const* members, int32_t n, const kf_batch_config* cfg, kf_batch** out) {
@@ -291,13 +309,12 @@ kf_status kf_batch_create(kf_ctx* const* members, int32_t n, const kf_batch_conf
   for (int i = 0; i < n; ++i) {
     const kf_ctx* c = members[i];
     if (c->cfg.pipeline_frames || c->cfg.precision != c0->cfg.precision || c->cfg.pattern != c0->cfg.pattern ||
-        c->cfg.n_samples != c0->cfg.n_samples || c->tiling.threads != c0->tiling.threads ||
+        c->cfg.n_samples != c0->cfg.n_samples || c->tiling.base_threads != c0->tiling.base_threads ||
         solve_pipelined(c->cfg) != solve_pipelined(c0->cfg) || c->device != c0->device ||
         c->stream != reinterpret_cast<hipStream_t>(cfg->stream))
       return KF_ERR_ARG;
   }
-  const int members_total = total_members(members, n);
-  const DynLayout dl = dyn_layout(n, members_total);
+  const DynLayout dl = dyn_layout(members, n);
   if (!cfg->workspace) return KF_ERR_ARG;
   if (cfg->workspace_bytes < static_bytes(n) + dl.total) return KF_ERR_OOM;
   if (reinterpret_cast<uintptr_t>(cfg->workspace) % 256 != 0) return KF_ERR_ARG;
@@ -311,9 +328,6 @@ kf_status kf_batch_create(kf_ctx* const* members, int32_t n, const kf_batch_conf
   b->pattern = c0->cfg.pattern;
   b->ns = c0->cfg.n_samples;
   b->threads = c0->tiling.threads;
-  b->pipelined = solve_pipelined(c0->cfg);
-  b->kind = b->pipelined ? 1 : 0;
-  for (int i = 0; i < n; ++i) b->kind |= solve_kind(members[i]->cfg) & 2;
   b->use_graph = cfg->use_graph != 0;
   b->cus = device_cus(c0->device);
   b->dl = dl;
@@ -321,27 +335,37 @@ kf_status kf_batch_create(kf_ctx* const* members, int32_t n, const kf_batch_conf
   b->d_so = reinterpret_cast<SolveArgs*>(ws);
   b->d_dyn = ws + static_bytes(n);
 
-  int maxB = 0;
-  size_t smem = 0;
-  for (kf_ctx* c : b->m) {
+  // each family's kernel holds its largest member: pixels per thread, LDS (team
+  // partials and the arrays of its tile), and the variants' branches if any member
+  // has them
+  int blocks[FAMILIES] = {}, largest[FAMILIES] = {};
+  for (const kf_ctx* c : b->m) {
+    const int f = family_of(c->tiling);
+    SolveKernel& k = b->fam[f].k;
+    k.prec = b->prec;
+    k.threads = c->tiling.threads;
+    k.sstep = c->tiling.s != 0;
+    k.ppt = std::max(k.ppt, c->tiling.ppt);
+    k.kind |= solve_kind(c->cfg);
     b->ppt = std::max(b->ppt, c->tiling.ppt);
-    maxB = std::max(maxB, c->tiling.blocks);
-    smem = std::max(smem, solve_smem_bytes(b->prec, c->tiling));
+    b->fam[f].smem = std::max(b->fam[f].smem, solve_smem_bytes(b->prec, c->tiling));
+    blocks[f] += c->tiling.blocks;
+    largest[f] = std::max(largest[f], c->tiling.blocks);
   }
-  if (!solve_batch_supported(b->prec, b->threads, b->ppt)) {
-    delete b;
-    return KF_ERR_ARG;
+  int full_queue = 0;
+  const std::vector<int> everyone = all_members(b);
+  for (int f = 0; f < FAMILIES; ++f) {
+    Family& fam = b->fam[f];
+    if (!blocks[f]) continue;
+    const int capacity = solve_batch_supported(fam.k) ? solve_batch_coresident(fam.k, fam.smem, b->device) : 0;
+    if (capacity < largest[f]) {
+      delete b;
+      return KF_ERR_ARG;
+    }
+    fam.grid = std::min(capacity, blocks[f]);
+    schedule(b, f, everyone);
+    full_queue = std::max(full_queue, fam.max_queue);
   }
-  // LDS: the largest member's need (team partials + the three rings of its tile)
-  b->smem = smem;
-  b->capacity = solve_batch_coresident(b->prec, b->threads, b->ppt, b->kind, b->smem, b->device);
-  if (b->capacity < maxB) {
-    delete b;
-    return KF_ERR_ARG;
-  }
-  b->grid = std::min(b->capacity, members_total);
-  schedule(b, all_members(b));
-  const int full_queue = b->max_queue;
 
   std::vector<SolveArgs> so(n);
   for (int i = 0; i < n; ++i) {
@@ -378,10 +402,13 @@ const char* kf_batch_last_error(const kf_batch* b) {
 
 kf_status kf_batch_layout(const kf_batch* b, int32_t out[4]) {
   if (!b || !out) return KF_ERR_ARG;
-  out[0] = b->grid;
+  out[0] = out[3] = 0;   // the largest launch, where the members take several kernels
   out[1] = b->threads;
   out[2] = b->ppt;
-  out[3] = b->max_queue;
+  for (const Family& f : b->fam) {
+    out[0] = std::max(out[0], f.grid);
+    out[3] = std::max(out[3], f.max_queue);
+  }
   return KF_OK;
 }
 

@@ -108,6 +108,10 @@ struct Layout {
 // Solver decomposition: tiles_x x tiles_y workgroups, each owning one tile.
 struct Tiling {
   int tiles_x, tiles_y, tile_w, tile_h, blocks, ppt, threads;
+  int s;       // CG iterations per team synchronisation of the s-step solver (kf_sstep.h); 0: kf_solve.hip
+  int rows;    // s-step solver: vertically adjacent pixels of the extended tile per thread
+  int cells;   // s-step solver: LDS cells of one array over the extended tile and its guard ring
+  int base_threads;   // the workgroup size that kf_solve.hip would take
 };
 
 constexpr int NV_MAX = 3;            // values reduced per synchronisation
@@ -116,8 +120,12 @@ constexpr int MAX_TEAM = 256;        // workgroups per keyframe team
 constexpr int CHUNK = 256;           // pixels per compaction chunk
 #define KF_BATCH_MAX KF_BATCH_MAX_MEMBERS
 
-bool choose_tiling(int W, int H, int tx_req, int ty_req, int threads_req, int prec, Tiling* t);
-double iteration_us(const Tiling& t);   // latency model of one PCG iteration
+// The decomposition of a configuration: the s-step solver's where it applies.
+bool choose_tiling(const kf_config& c, Tiling* t);
+// kf_solve.hip's alone.
+bool choose_tiling_classic(int W, int H, int tx_req, int ty_req, int threads_req, int prec, Tiling* t);
+double iteration_us(const Tiling& t);   // latency model of one PCG iteration (kf_solve.hip)
+double sstep_gn_us(const Tiling& t, int n_cg);   // of one Gauss-Newton iteration (s-step solver)
 // Workgroups of this tiling the device can hold at once (0 if unknown).
 // kind: bit 0 pipelined CG, bit 1 the solver instantiation that handles the
 // Sec. III variants and the keyframe rule (solve_kind)
@@ -182,6 +190,7 @@ struct SolveArgs {
   DevScalars* scal;
   uint64_t* parts;           // [2][NV_MAX][PART_REPLICAS][blocks][2] exchange words
   uint64_t* halo;            // [2][blocks][2 perim][2]: first, then second row / column per side
+  int s, rows, cells;        // s-step solver (Tiling)
   int perim;                 // 2 tile_w + 2 tile_h
   int ghost_z;               // 1: fixed-count pipelined CG on tiles >= 2 x 2 without the
                              // initial-residual synchronisation (x shipped two pixels deep)
@@ -227,17 +236,33 @@ hipError_t launch_solve(int prec, const Tiling& t, const SolveArgs& a, bool coop
 // Batched solver: workgroup g runs the team members queue[qoff[g] .. qoff[g+1])
 // in order, each entry (keyframe << 8) | member; all `grid` workgroups must be
 // co-resident.
-hipError_t launch_solve_batch(int prec, int threads, int ppt, int kind, const SolveArgs* tab,
-                              const int32_t* queue, const int32_t* qoff, int grid, size_t smem, hipStream_t s);
+struct SolveKernel {         // one kernel of the batched solver
+  int prec, threads, ppt, kind;
+  bool sstep;                // s-step solver (else kf_solve.hip, which goes by threads and ppt)
+};
+hipError_t launch_solve_batch(const SolveKernel& k, const SolveArgs* tab, const int32_t* queue, const int32_t* qoff,
+                              int grid, size_t smem, hipStream_t s);
 // Team-synchronisation probe on the layout of `a` (see k_sync_probe).
 hipError_t launch_sync_probe(int prec, const Tiling& t, const SolveArgs& a, int rounds, int nv, hipStream_t s);
-int solve_batch_coresident(int prec, int threads, int ppt, int kind, size_t smem, int device);
-bool solve_batch_supported(int prec, int threads, int ppt);
+int solve_batch_coresident(const SolveKernel& k, size_t smem, int device);
+bool solve_batch_supported(const SolveKernel& k);
 hipError_t launch_read(int prec, const ReadArgs& a, hipStream_t s);
 hipError_t launch_import(int prec, const ImportArgs& a, hipStream_t s);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_set_u32(uint32_t* p, uint32_t v, hipStream_t s);
 size_t solve_smem_bytes(int prec, const Tiling& t);
+// Pixels per thread that the s-step solver has kernels for, by s.
+#define KF_SS2_ROWS(M) M(4) M(6) M(8) M(10) M(12) M(14)
+#define KF_SS4_ROWS(M) M(1) M(2) M(3) M(4)
+// s-step solver kernels (nullptr: none holds that many rows per thread).
+const void* sstep2_fn(int rows, bool var);
+const void* sstep4_fn(int rows, bool var);
+const void* sstep_batch_fn(bool var);
+size_t sstep_smem_bytes(const Tiling& t);
+// Exchange words of one tile's boundary frame, s + 1 pixels deep, per plane.
+__host__ __device__ inline int sstep_frame_words(int tile_w, int tile_h, int s) {
+  return (2 * (s + 1) * (tile_w + tile_h) + 15) & ~15;
+}
 // Compute units of the device (256 if the query fails).
 int device_cus(int device);
 

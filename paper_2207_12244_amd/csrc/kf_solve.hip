@@ -24,7 +24,7 @@
 // synchronisation: its scale step ships x two pixels deep (plus the diagonal
 // neighbours' corner pixels), from which each member assembles the ghost
 // values of the first stencil operand itself.
-#include "kf_internal.h"
+#include "kf_device.h"
 
 namespace kf {
 
@@ -33,41 +33,12 @@ namespace {
 constexpr int GMAX = 2;      // ghost slots per thread: ghost ring <= GMAX * threads cells
 constexpr int G2MAX = 1;     // second-ring slots per thread: second ring + 4 corners <= threads cells
 
-__device__ inline void st_word(KF_GLOBAL uint64_t* p, uint64_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline uint64_t ld_word(const KF_GLOBAL uint64_t* p) {
-  return __hip_atomic_load(const_cast<KF_GLOBAL uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// Compiler-only barrier (no instruction): the value counts as redefined here,
-// so per-pixel addresses derived from it are recomputed inside the loop that
-// holds the barrier instead of being hoisted and kept live in registers for the
-// whole launch (that cut the register count per pixel from ~53 to ~16).
-__device__ inline void refresh(int& v) { asm volatile("" : "+v"(v)); }
-
-__device__ inline uint64_t tagged(uint32_t bits, uint32_t e) { return ((uint64_t)e << 32) | (uint64_t)bits; }
-
 template <typename V> struct Wire;
 template <> struct Wire<float> {
   static constexpr int N = 1;
   __device__ static void put(KF_GLOBAL uint64_t* w, float v, uint32_t e) { st_word(w, tagged(__float_as_uint(v), e)); }
   __device__ static float make(uint32_t lo, uint32_t) { return __uint_as_float(lo); }
 };
-// One-word transport of an FP64 partial: the top 48 bits of the double
-// (rounded; relative precision 2^-37) and a 16-bit epoch. Used when a launch
-// spans fewer than 30000 epochs, so a slot's previous content is never 2^16
-// epochs old.
-struct Packed48 {
-  __device__ static uint64_t make_word(double v, uint32_t e) {
-    const uint64_t b = (uint64_t)__double_as_longlong(v) + 0x8000ull;
-    return ((uint64_t)(e & 0xffffu) << 48) | (b >> 16);
-  }
-  __device__ static bool ready(uint64_t w, uint32_t e) { return (uint32_t)(w >> 48) == (e & 0xffffu); }
-  __device__ static double value(uint64_t w) {
-    return __longlong_as_double((long long)((w & 0xffffffffffffull) << 16));
-  }
-};
-
 template <> struct Wire<double> {
   static constexpr int N = 2;
   __device__ static void put(KF_GLOBAL uint64_t* w, double v, uint32_t e) {
@@ -79,48 +50,6 @@ template <> struct Wire<double> {
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
   }
 };
-
-// Data-parallel-primitive move of both halves of a double (out-of-row lanes read 0).
-template <int CTRL, int ROW_MASK, bool BOUND_ZERO>
-__device__ inline double dpp_d(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, ROW_MASK, 0xf, BOUND_ZERO);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROW_MASK, 0xf, BOUND_ZERO);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// Sum over the 64 lanes in a fixed order: an inclusive scan inside each
-// 16-lane row (shifts 1, 2, 4, 8), then the row totals are carried with the
-// row broadcasts 15 and 31; lane 63 ends with the total (other lanes hold
-// partial sums).
-__device__ inline double wave_total_lane63(double v) {
-  v += dpp_d<0x111, 0xf, true>(v);   // row_shr:1
-  v += dpp_d<0x112, 0xf, true>(v);   // row_shr:2
-  v += dpp_d<0x114, 0xf, true>(v);   // row_shr:4
-  v += dpp_d<0x118, 0xf, true>(v);   // row_shr:8
-  v += dpp_d<0x142, 0xa, false>(v);  // row_bcast:15 into rows 1 and 3
-  v += dpp_d<0x143, 0xc, false>(v);  // row_bcast:31 into rows 2 and 3
-  return v;
-}
-
-// IRLS weight of a whitened residual: Huber min(1, c / |r|), or Tukey's
-// biweight (1 - (r/c)^2)^2 inside c and 0 beyond.
-template <typename T>
-__device__ inline T huber_w(T r, T delta, bool tukey = false) {
-  if (tukey) {
-    const T t = r / delta, t2 = t * t;
-    return t2 <= (T)1 ? ((T)1 - t2) * ((T)1 - t2) : (T)0;
-  }
-  const T a = fabs(r);
-  return a <= delta ? (T)1 : delta / a;
-}
-
-// IRLS weight of the gradient edge between x_a and its right / lower neighbour x_b.
-template <typename T>
-__device__ inline T edge_weight(T xa, T xb, T g, T isd, T delta, bool tukey) {
-  const T r = ((xb - xa) - g) * isd;
-  return huber_w(r, delta, tukey) * isd * isd;
-}
 
 template <typename T, int NT>
 struct Team {
@@ -1189,23 +1118,22 @@ const void* batch_fn(int prec, int threads, int ppt, int kind) {
   return prec == KF_F64 ? batch_fn_t<double>(threads, ppt, kind) : batch_fn_t<float>(threads, ppt, kind);
 }
 
-template <typename T>
-hipError_t solve_t(const Tiling& t, const SolveArgs& a, bool cooperative, int kind, hipStream_t s) {
-  const size_t sm = smem_for(sizeof(T), t);
-  void* args[] = {const_cast<SolveArgs*>(&a)};
-  const void* fn = solve_fn<T>(t, kind);
-  if (!fn) return hipErrorInvalidValue;
-  if (sm > 48 * 1024) {
-    hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-    if (err != hipSuccess) return err;
-  }
-  if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(t.blocks), dim3(t.threads), args, (unsigned)sm, s);
-  return hipLaunchKernel(fn, dim3(t.blocks), dim3(t.threads), args, (unsigned)sm, s);
+const void* kernel_of(int prec, const Tiling& t, int kind) {
+  if (t.s == 2) return sstep2_fn(t.rows, (kind & 2) != 0);
+  if (t.s == 4) return sstep4_fn(t.rows, (kind & 2) != 0);
+  return prec == KF_F64 ? solve_fn<double>(t, kind) : solve_fn<float>(t, kind);
+}
+
+const void* batch_kernel_of(const SolveKernel& k) {
+  if (k.sstep) return sstep_batch_fn((k.kind & 2) != 0);
+  return batch_fn(k.prec, k.threads, k.ppt, k.kind);
 }
 
 }  // namespace
 
-size_t solve_smem_bytes(int prec, const Tiling& t) { return smem_for(prec == KF_F64 ? 8 : 4, t); }
+size_t solve_smem_bytes(int prec, const Tiling& t) {
+  return t.s ? sstep_smem_bytes(t) : smem_for(prec == KF_F64 ? 8 : 4, t);
+}
 
 // Workgroups of kernel fn the device holds at once with `smem` bytes of LDS
 // each; 0 (and the runtime's error state cleared) if a query fails.
@@ -1223,14 +1151,22 @@ int coresident_of(const void* fn, int threads, size_t smem, int device) {
 }
 
 int solve_max_coresident(int prec, const Tiling& t, int kind, int device) {
-  const void* fn = prec == KF_F64 ? solve_fn<double>(t, kind) : solve_fn<float>(t, kind);
+  const void* fn = kernel_of(prec, t, kind);
   if (!fn) return 0;
   return coresident_of(fn, t.threads, solve_smem_bytes(prec, t), device);
 }
 
 hipError_t launch_solve(int prec, const Tiling& t, const SolveArgs& a, bool cooperative, int kind, hipStream_t s) {
-  if (prec == KF_F64) return solve_t<double>(t, a, cooperative, kind, s);
-  return solve_t<float>(t, a, cooperative, kind, s);
+  const size_t sm = solve_smem_bytes(prec, t);
+  void* args[] = {const_cast<SolveArgs*>(&a)};
+  const void* fn = kernel_of(prec, t, kind);
+  if (!fn) return hipErrorInvalidValue;
+  if (sm > 48 * 1024) {
+    hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+    if (err != hipSuccess) return err;
+  }
+  if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(t.blocks), dim3(t.threads), args, (unsigned)sm, s);
+  return hipLaunchKernel(fn, dim3(t.blocks), dim3(t.threads), args, (unsigned)sm, s);
 }
 
 hipError_t launch_sync_probe(int prec, const Tiling& t, const SolveArgs& a, int rounds, int nv, hipStream_t s) {
@@ -1244,7 +1180,7 @@ hipError_t launch_sync_probe(int prec, const Tiling& t, const SolveArgs& a, int 
          : t.threads == 512 ? reinterpret_cast<const void*>(&k_sync_probe<float, 512>)
                             : reinterpret_cast<const void*>(&k_sync_probe<float, 1024>);
   }
-  const size_t sm = solve_smem_bytes(prec, t);
+  const size_t sm = smem_for(prec == KF_F64 ? 8 : 4, t);
   if (sm > 48 * 1024) {
     hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
     if (err != hipSuccess) return err;
@@ -1253,20 +1189,20 @@ hipError_t launch_sync_probe(int prec, const Tiling& t, const SolveArgs& a, int 
   return hipLaunchKernel(fn, dim3(t.blocks), dim3(t.threads), args, (unsigned)sm, s);
 }
 
-bool solve_batch_supported(int prec, int threads, int ppt) { return batch_fn(prec, threads, ppt, 1) != nullptr; }
+bool solve_batch_supported(const SolveKernel& k) { return batch_kernel_of(k) != nullptr; }
 
-int solve_batch_coresident(int prec, int threads, int ppt, int kind, size_t smem, int device) {
-  const void* fn = batch_fn(prec, threads, ppt, kind);
+int solve_batch_coresident(const SolveKernel& k, size_t smem, int device) {
+  const void* fn = batch_kernel_of(k);
   if (!fn) return 0;
-  return coresident_of(fn, threads, smem, device);
+  return coresident_of(fn, k.threads, smem, device);
 }
 
-hipError_t launch_solve_batch(int prec, int threads, int ppt, int kind, const SolveArgs* tab,
-                              const int32_t* queue, const int32_t* qoff, int grid, size_t smem, hipStream_t s) {
-  const void* fn = batch_fn(prec, threads, ppt, kind);
+hipError_t launch_solve_batch(const SolveKernel& k, const SolveArgs* tab, const int32_t* queue, const int32_t* qoff,
+                              int grid, size_t smem, hipStream_t s) {
+  const void* fn = batch_kernel_of(k);
   if (!fn || grid < 1) return hipErrorInvalidValue;
   void* args[] = {const_cast<SolveArgs**>(&tab), const_cast<int32_t**>(&queue), const_cast<int32_t**>(&qoff)};
-  return hipLaunchKernel(fn, dim3(grid), dim3(threads), args, (unsigned)smem, s);
+  return hipLaunchKernel(fn, dim3(grid), dim3(k.threads), args, (unsigned)smem, s);
 }
 
 }  // namespace kf

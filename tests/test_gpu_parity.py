@@ -5,7 +5,7 @@ import pytest
 
 import kfsynth
 from oracle import fusion, stereo
-from oracle.fusion import SolverParams
+from oracle.fusion import PriorMaps, SolverParams
 from oracle.stereo import StereoParams, UPDATED
 
 import gpu_util as gu
@@ -410,3 +410,51 @@ def test_frame_pipelining_gives_the_same_results(c1_short):
         assert np.array_equal(a[k].cpu().numpy(), b[k].cpu().numpy()), k
         assert np.array_equal(ma[0][k].cpu().numpy(), mb[0][k].cpu().numpy()), k
     assert a["tau"] == b["tau"] and (ua, va) == (ub, vb)
+
+
+@pytest.mark.parametrize("W,H,tiles,n_cg,syncs", [
+    (8, 8, (1, 1), 100, None),       # more iterations than unknowns: CG converges and ends early
+    (16, 16, (1, 1), 3, 1),          # 1 row per thread, one block of fewer iterations than it could make
+    (31, 24, (1, 1), 7, 2),          # a remainder in the last block, one workgroup
+    (41, 31, (9, 7), 20, 5),         # last column and row of tiles 1 px wide and high
+    (43, 33, (2, 11), 10, 5),        # tiles 3 px high: 2 iterations per synchronisation
+    (130, 110, (15, 11), 20, 5),     # more members than a wavefront polls in one pass
+    (64, 48, (1, 1), 9, 5),          # strips of 8 rows, no neighbour tile
+    (150, 37, (3, 1), 20, 10),       # neighbours on two sides only
+    (96, 80, (2, 2), 6, 3),          # strips of 6 rows
+    (120, 96, (2, 2), 6, 3),         # strips of 8 rows with neighbours
+    (128, 120, (2, 2), 6, 3),        # strips of 10 rows
+    (160, 120, (2, 2), 20, 10),      # strips of 12 rows
+    (168, 120, (2, 2), 20, 10),      # strips of 14 rows, the longest
+    (151, 125, (16, 16), 20, 5),     # the largest team, tiles 1 px wide at the right
+])
+def test_solver_sstep_shapes(W, H, tiles, n_cg, syncs):
+    """The s-step solver (automatic form, fixed count, float) at the edges of its
+    tilings against the oracle's iteration-matched solve: team sizes, strip
+    lengths, ragged tiles, last blocks of fewer iterations, and CG that ends
+    early. Tolerance: that of the other float solves (x of order 1 through at
+    most 3 x 20 float32 iterations)."""
+    gu.say(f"[solver-sstep] {W}x{H} tiles {tiles} n_cg {n_cg}")
+    rng = np.random.default_rng(W * 1000 + H)
+    prior = PriorMaps(rng.normal(0.5, 0.3, (H, W)), rng.uniform(0.01, 0.2, (H, W)), rng.normal(0, 0.05, (H, W)),
+                      rng.uniform(1e-3, 1e-2, (H, W)), rng.normal(0, 0.05, (H, W)), rng.uniform(1e-3, 1e-2, (H, W)))
+    has = rng.random((H, W)) < 0.3
+    rho = np.where(has, rng.uniform(0.3, 1.2, (H, W)), 0.0).astype(np.float32)
+    var = np.where(has, rng.uniform(1e-4, 1e-2, (H, W)), 0.0).astype(np.float32)
+    from paper_2207_12244_amd.kf import Keyframe
+    t = gu.torch()
+    K = np.array([[0.8 * W, 0.0, W / 2.0], [0.0, 0.8 * W, H / 2.0], [0.0, 0.0, 1.0]])
+    kf = Keyframe(W, H, precision="f32", n_gn=3, n_cg=n_cg, K=K, tiles=tiles)
+    kf.set_prior(gu.dev(np.zeros((H, W)), t.uint8), *[gu.dev(m, t.float32) for m in vars(prior).values()], np.eye(4))
+    kf.import_state(rho=gu.dev(rho, t.float32), var=gu.dev(var, t.float32))
+    kf.solve()
+    st = kf.export_state()
+    maps = PriorMaps(*[np.asarray(m, np.float32).astype(np.float64) for m in vars(prior).values()])
+    x_o, tau_o, _ = fusion.gauss_newton(maps.mu, 0.0, maps, gu.oracle_semi(rho.astype(np.float64), var.astype(np.float64)),
+                                        SolverParams(n_gn=3, n_cg=n_cg, linear_solver="pcg"))
+    err = np.abs(st["x"].cpu().numpy().astype(np.float64) - x_o)
+    gu.say(f"[solver-sstep] max|dx| {err.max():.3e} rms {np.sqrt(np.mean(err ** 2)):.3e} "
+           f"dtau {abs(st['tau'] - tau_o):.3e} syncs {kf.stats().team_syncs}")
+    if syncs is not None:
+        assert kf.stats().team_syncs == 3 * (syncs + 1)   # per GN iteration: the blocks and the scale step
+    assert err.max() <= 2e-4 and np.sqrt(np.mean(err ** 2)) <= 2e-5 and abs(st["tau"] - tau_o) <= 2e-5
