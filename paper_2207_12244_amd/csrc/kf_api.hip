@@ -469,6 +469,7 @@ void solve_args(kf_ctx* c, SolveArgs* a) {
   a->s = c->tiling.s;
   a->rows = c->tiling.rows;
   a->cells = c->tiling.cells;
+  a->keep = !c->tiling.s && solve_keeps(g.precision == KF_F64 ? 8 : 4, c->tiling) ? 1 : 0;
   a->perim = 2 * c->tiling.tile_w + 2 * c->tiling.tile_h;
   // the second-ring cells (perimeter + 4 corners) fit one slot per thread
   a->ghost_z = (solve_pipelined(g) && g.cg_rtol == 0.0 && c->tiling.tile_w >= 2 && c->tiling.tile_h >= 2 &&

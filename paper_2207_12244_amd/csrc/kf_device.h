@@ -35,6 +35,13 @@ struct Packed48 {
   }
 };
 
+// v as it is, not to be fused with what uses it.
+template <typename T>
+__device__ inline T rounded(T v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
 // Data-parallel-primitive move of both halves of a double (out-of-row lanes read 0).
 template <int CTRL, int ROW_MASK, bool BOUND_ZERO>
 __device__ inline double dpp_d(double v) {

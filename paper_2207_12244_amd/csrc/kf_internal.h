@@ -191,6 +191,7 @@ struct SolveArgs {
   uint64_t* parts;           // [2][NV_MAX][PART_REPLICAS][blocks][2] exchange words
   uint64_t* halo;            // [2][blocks][2 perim][2]: first, then second row / column per side
   int s, rows, cells;        // s-step solver (Tiling)
+  int keep;                  // 1: the LDS holds the own pixels' semi-dense measurements (solve_keeps)
   int perim;                 // 2 tile_w + 2 tile_h
   int ghost_z;               // 1: fixed-count pipelined CG on tiles >= 2 x 2 without the
                              // initial-residual synchronisation (x shipped two pixels deep)
@@ -251,6 +252,7 @@ hipError_t launch_import(int prec, const ImportArgs& a, hipStream_t s);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_set_u32(uint32_t* p, uint32_t v, hipStream_t s);
 size_t solve_smem_bytes(int prec, const Tiling& t);
+bool solve_keeps(size_t elt, const Tiling& t);
 // Pixels per thread that the s-step solver has kernels for, by s.
 #define KF_SS2_ROWS(M) M(4) M(6) M(8) M(10) M(12) M(14)
 #define KF_SS4_ROWS(M) M(1) M(2) M(3) M(4)

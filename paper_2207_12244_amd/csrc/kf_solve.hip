@@ -228,6 +228,11 @@ struct Team {
     unsigned spins = 0;
     uint64_t t0 = 0;
     bool ok = true;
+    // No word is here yet, and a load that comes too early costs a second trip
+    // and traffic that the words wait behind: sleep for ~0.2 of the ~0.6 us
+    // (640 x 480 solve on 256 tiles: 622 us at half of it, 562 with it, 599 at
+    // twice that; 160 x 120 FP64 in the tolerance mode: 762, 687, 721).
+    if (B > 1) __builtin_amdgcn_s_sleep(8);
     while (true) {
       bool all = true;
 #pragma unroll
@@ -337,7 +342,8 @@ struct Team {
 // partials, abort flag, then three rings of (tile_h + 2) x (tile_w + 2):
 // x and two stencil operands, then the second ring of x (2 tile_w + 2 tile_h:
 // top, bottom, left, right; its corners sit in the corner cells of the x ring),
-// then 12 x (2 tile_w + 2 tile_h) static row inputs of the ghost cells.
+// then 12 x (2 tile_w + 2 tile_h) static row inputs of the ghost cells and, if
+// a.keep, 2 x tile_w tile_h semi-dense measurements of the own pixels.
 template <typename T, int NT>
 struct MemberLds {
   T* xs;
@@ -501,13 +507,21 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
   const KF_GLOBAL T* var_g = gp(static_cast<const T*>(a.var));
 
   // per-pixel registers; pixel j of this thread is k = tid + j NT of the tile
-  int lxy[PPT];   // (ly << 16) | lx, or -1 when the thread has no j-th pixel
+  // its ring index, or 0 when the thread has no j-th pixel: a corner cell, which
+  // no pixel's stencil reads (its own reads the ring before it in LDS). The loops
+  // below make no difference between the two: such a slot's coefficients and
+  // vectors are 0, and its corner cell gets their 0. A branch per pixel would
+  // wait for each pixel's loads alone (512 x 10 px of 4 tiles of 160 x 120: 908
+  // against 838 us a solve, with the rows' inputs loaded several pixels at a
+  // time and the semi-dense measurement kept in LDS).
+  int li[PPT];
   T xr[PPT], rr[PPT], pv[PPT], dg[PPT], idg[PPT], cR[PPT], cL[PPT], cD[PPT], cU[PPT];
   const T r_floor = (T)a.r_floor;
-#define KF_LX(j) (lxy[j] & 0xffff)
-#define KF_LY(j) (lxy[j] >> 16)
-#define KF_LI(j) ((KF_LY(j) + 1) * rw + KF_LX(j) + 1)
-#define KF_GI(j) ((oy + KF_LY(j)) * W + ox + KF_LX(j))
+  const uint32_t inv_rw = 0xffffffffu / (uint32_t)rw + 1u;   // li / rw as a high product: exact for li < 2^16
+#define KF_ROW(j) ((int)__umulhi((uint32_t)li[j], inv_rw))
+#define KF_V(j) (oy + max(KF_ROW(j) - 1, 0))                  // image row and column; without a pixel: of the tile's first
+#define KF_U(j) (ox + max(li[j] - KF_ROW(j) * rw - 1, 0))
+#define KF_GI(j) (KF_V(j) * W + KF_U(j))
   // Table III drops the gradient terms; Table II solves a scale-ambiguous
   // log-depth y = x - tau from the semi-dense and gradient terms (tau held at
   // 0 inside the GN loop) and fits the scale afterwards
@@ -524,11 +538,11 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
 #pragma unroll
   for (int j = 0; j < PPT; ++j) {
     const int k = tid + j * NT;
-    lxy[j] = k < npx ? (((k / tw) << 16) | (k % tw)) : -1;
+    li[j] = k < npx ? (k / tw + 1) * rw + k % tw + 1 : 0;
     xr[j] = rr[j] = pv[j] = dg[j] = idg[j] = cR[j] = cL[j] = cD[j] = cU[j] = (T)0;
-    if (lxy[j] >= 0) {
+    if (li[j] > 0) {
       xr[j] = x_g[KF_GI(j)] - x_shift;
-      xs[KF_LI(j)] = xr[j];
+      xs[li[j]] = xr[j];
     }
   }
   // ghost x straight from the state (consistent at launch)
@@ -564,6 +578,11 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
   double vals[NV_MAX], tot[NV_MAX];
   T gval[GMAX];
 
+  T* x2 = lds.x2;
+  const int perim = a.perim;
+  T* gdat = lds.gdat;   // [12][perim]: the ghost cells' RowData, filled once per launch
+  const int keep_n = a.tile_w * a.tile_h;
+
   // semi-dense measurement in log space (Sec. II-B last step): z = -ln rho,
   // R = max(v / rho^2, R_floor); returns 1/sqrt(R), 0 when the pixel has none
   auto semi = [&](int gi, T& z) -> T {
@@ -579,6 +598,28 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
     return (T)1 / sqrt(R);
   };
 
+  // Read once per launch where the LDS has room for it: z and 1/sqrt(R) of the
+  // own pixels (slot k = tid + j NT).
+  T* zs_l = a.keep ? gdat + 12 * perim : nullptr;
+  if (a.keep) {
+#pragma unroll
+    for (int j = 0; j < PPT; ++j) {
+      const int k = tid + j * NT;
+      if (li[j] <= 0) continue;
+      T z;
+      zs_l[keep_n + k] = semi(KF_GI(j), z);
+      zs_l[k] = z;
+    }
+  }
+  auto semi_own = [&](int j, T& z) -> T {   // of own pixel j, 0 without one
+    z = (T)0;
+    if (!a.keep) return li[j] > 0 ? semi(KF_GI(j), z) : (T)0;
+    const int k = min(tid + j * NT, keep_n - 1);
+    const T isr = zs_l[keep_n + k];
+    z = li[j] > 0 ? zs_l[k] : (T)0;
+    return li[j] > 0 ? isr : (T)0;
+  };
+
   // The static inputs of one row of the 5-point normal equations at pixel
   // i = (u, v): network log-depth and its inverse sigma, the semi-dense
   // measurement, and per gradient edge (right, left, lower, upper) the prior
@@ -586,25 +627,28 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
   struct RowData {
     T mu, isn, zs, isr, gR, sR, gL, sL, gD, sD, gU, sU;
   };
+  // (all but the semi-dense measurement; loads without branches, so that those
+  // of several pixels are in flight together)
   auto row_data = [&](int i, int u, int v) -> RowData {
     RowData r;
     r.mu = mu_g[i];
     r.isn = isn_g[i];
-    r.isr = semi(i, r.zs);
-    r.gR = r.sR = r.gL = r.sL = r.gD = r.sD = r.gU = r.sU = (T)0;
-    if (u < W - 1) {
-      r.gR = gx_g[i]; r.sR = isgx_g[i];
-    }
-    if (u > 0) {
-      r.gL = gx_g[i - 1]; r.sL = isgx_g[i - 1];
-    }
-    if (v < H - 1) {
-      r.gD = gy_g[i]; r.sD = isgy_g[i];
-    }
-    if (v > 0) {
-      r.gU = gy_g[i - W]; r.sU = isgy_g[i - W];
-    }
+    r.gR = gx_g[i];
+    r.sR = isgx_g[i];
+    const int il = i - (u > 0 ? 1 : 0), iu = i - (v > 0 ? W : 0);
+    r.gL = gx_g[il];
+    r.sL = isgx_g[il];
+    r.gD = gy_g[i];
+    r.sD = isgy_g[i];
+    r.gU = gy_g[iu];
+    r.sU = isgy_g[iu];
     return r;
+  };
+  auto mask_edges = [&](RowData& r, int u, int v) {
+    if (!(u < W - 1)) r.gR = r.sR = (T)0;
+    if (!(u > 0)) r.gL = r.sL = (T)0;
+    if (!(v < H - 1)) r.gD = r.sD = (T)0;
+    if (!(v > 0)) r.gU = r.sU = (T)0;
   };
 
   // The row (Sec. II-C) at log-depth xi with its right / left / lower / upper
@@ -615,30 +659,23 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
   struct Row {
     T wn, ws, bb, cr, cl, cd, cu, d;
   };
-  auto row_at = [&](const RowData& r, int u, int v, T xi, T xR, T xL, T xD, T xU, bool edges) -> Row {
+  // (An edge that leaves the image, and a missing measurement, has inverse sigma
+  // 0 and so weight 0. `rounded` keeps a weight from being fused into the sums.)
+  auto row_at = [&](const RowData& r, T xi, T xR, T xL, T xD, T xU, bool edges) -> Row {
     Row q;
-    q.wn = postfit ? (T)0 : huber_w((xi - r.mu) * r.isn, delta, tukey) * r.isn * r.isn;
-    q.ws = (T)0;
-    if (r.isr > (T)0) q.ws = huber_w((xi - (T)tau - r.zs) * r.isr, delta, tukey) * r.isr * r.isr;
+    q.wn = postfit ? (T)0 : rounded(huber_w((xi - r.mu) * r.isn, delta, tukey) * r.isn * r.isn);
+    q.ws = rounded(huber_w((xi - (T)tau - r.zs) * r.isr, delta, tukey) * r.isr * r.isr);
     T bb = q.wn * r.mu + q.ws * ((T)tau + r.zs);
     T cr = 0, cl = 0, cd = 0, cu = 0;
     if (edges) {
-      if (u < W - 1) {
-        cr = edge_weight(xi, xR, r.gR, r.sR, delta, tukey);
-        bb -= cr * r.gR;
-      }
-      if (u > 0) {
-        cl = edge_weight(xL, xi, r.gL, r.sL, delta, tukey);
-        bb += cl * r.gL;
-      }
-      if (v < H - 1) {
-        cd = edge_weight(xi, xD, r.gD, r.sD, delta, tukey);
-        bb -= cd * r.gD;
-      }
-      if (v > 0) {
-        cu = edge_weight(xU, xi, r.gU, r.sU, delta, tukey);
-        bb += cu * r.gU;
-      }
+      cr = rounded(edge_weight(xi, xR, r.gR, r.sR, delta, tukey));
+      bb -= cr * r.gR;
+      cl = rounded(edge_weight(xL, xi, r.gL, r.sL, delta, tukey));
+      bb += cl * r.gL;
+      cd = rounded(edge_weight(xi, xD, r.gD, r.sD, delta, tukey));
+      bb -= cd * r.gD;
+      cu = rounded(edge_weight(xU, xi, r.gU, r.sU, delta, tukey));
+      bb += cu * r.gU;
     }
     q.bb = bb;
     q.cr = cr; q.cl = cl; q.cd = cd; q.cu = cu;
@@ -652,9 +689,6 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
   // every GN iteration. gz_c0: this thread's first ghost cell; the cells start
   // at the first wavefront whose threads hold one pixel fewer than PPT.
   const bool ghost_z = PIPE && !tol_mode && a.ghost_z != 0;
-  T* x2 = lds.x2;
-  T* gdat = lds.gdat;   // [12][perim]: the ghost cells' RowData, filled once per launch
-  const int perim = a.perim;
   int gz_c0;
   {
     const int full = npx - (PPT - 1) * NT;   // threads [0, full) hold PPT pixels
@@ -684,7 +718,9 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
       int gx, gy;
       if (ghost_cell(c, gx, gy) < 0) continue;
       const int u = ox + gx, v = oy + gy;
-      const RowData r = row_data(v * W + u, u, v);
+      RowData r = row_data(v * W + u, u, v);
+      r.isr = semi(v * W + u, r.zs);
+      mask_edges(r, u, v);
       const T vals12[12] = {r.mu, r.isn, r.zs, r.isr, r.gR, r.sR, r.gL, r.sL, r.gD, r.sD, r.gU, r.sU};
 #pragma unroll
       for (int k = 0; k < 12; ++k) gdat[k * perim + c] = vals12[k];
@@ -693,7 +729,7 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
 
   for (int gn = 0; gn < (new_kf ? 0 : a.n_gn); ++gn) {
 #pragma unroll
-    for (int j = 0; j < PPT; ++j) refresh(lxy[j]);
+    for (int j = 0; j < PPT; ++j) refresh(li[j]);
     // ---- IRLS weights and 5-point normal equations at (x, tau) (Sec. II-C);
     //      r = b - A x, z = r / diag, p = z
     double rz = 0.0, r2 = 0.0, b2 = 0.0;
@@ -717,43 +753,57 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
         const T xL = gx == -1 ? x2[2 * tw + gy] : xs[lg - 1];
         const T xD = gy == th ? x2[tw + gx] : xs[lg + rw];
         const T xU = gy == -1 ? x2[gx] : xs[lg - rw];
-        const int u = ox + gx, v = oy + gy;
         RowData r;
         r.mu = gdat[c]; r.isn = gdat[perim + c]; r.zs = gdat[2 * perim + c]; r.isr = gdat[3 * perim + c];
         r.gR = gdat[4 * perim + c]; r.sR = gdat[5 * perim + c]; r.gL = gdat[6 * perim + c];
         r.sL = gdat[7 * perim + c]; r.gD = gdat[8 * perim + c]; r.sD = gdat[9 * perim + c];
         r.gU = gdat[10 * perim + c]; r.sU = gdat[11 * perim + c];
-        const Row q = row_at(r, u, v, xg, xR, xL, xD, xU, true);
+        const Row q = row_at(r, xg, xR, xL, xD, xU, true);
         const T ig = q.d > (T)0 ? (T)1 / q.d : (T)0;
         const T ax = q.d * xg - q.cr * xR - q.cl * xL - q.cd * xD - q.cu * xU;
         ps[lg] = (q.bb - ax) * ig;
       }
     }
+    constexpr int CH = PPT <= 4 ? 2 : (PPT == 10 ? 5 : 3);   // pixels whose loads are in flight together
 #pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-      if (lxy[j] < 0) continue;
-      const int u = ox + KF_LX(j), v = oy + KF_LY(j);
-      const int i = KF_GI(j), l = KF_LI(j);
-      const T xi = xr[j];
-      const T xR = xs[l + 1], xL = xs[l - 1], xD = xs[l + rw], xU = xs[l - rw];
-      const Row q = row_at(row_data(i, u, v), u, v, xi, xR, xL, xD, xU, !nopair);
-      if (nopair) {
-        // per-pixel weighted mean of the network and semi-dense log-depths
-        if (q.wn + q.ws > (T)0) xr[j] = q.bb / (q.wn + q.ws);
-        continue;
+    for (int j0 = 0; j0 < PPT; j0 += CH) {
+      RowData rd[CH];
+#pragma unroll
+      for (int j = j0; j < j0 + CH && j < PPT; ++j) rd[j - j0] = row_data(KF_GI(j), KF_U(j), KF_V(j));
+#pragma unroll
+      for (int j = j0; j < j0 + CH && j < PPT; ++j) {
+        RowData& r_ = rd[j - j0];
+        r_.isr = semi_own(j, r_.zs);
+        mask_edges(r_, KF_U(j), KF_V(j));
+        const bool has = li[j] > 0;
+        const int l = has ? li[j] : rw + 1;   // without a pixel: the first one's row, not taken
+        const T xi = xs[l];
+        const T xR = xs[l + 1], xL = xs[l - 1], xD = xs[l + rw], xU = xs[l - rw];
+        const Row q = row_at(r_, xi, xR, xL, xD, xU, !nopair);
+        if (nopair) {
+          // per-pixel weighted mean of the network and semi-dense log-depths
+          if (has && q.wn + q.ws > (T)0) xr[j] = q.bb / (q.wn + q.ws);
+          continue;
+        }
+        const T id = q.d > (T)0 ? (T)1 / q.d : (T)0;   // d = 0 only without network and gradient terms
+        const T ax = q.d * xi - q.cr * xR - q.cl * xL - q.cd * xD - q.cu * xU;
+        const T r = has ? q.bb - ax : (T)0;
+        dg[j] = has ? q.d : (T)0;
+        idg[j] = has ? id : (T)0;
+        cR[j] = has ? q.cr : (T)0;
+        cL[j] = has ? q.cl : (T)0;
+        cD[j] = has ? q.cd : (T)0;
+        cU[j] = has ? q.cu : (T)0;
+        rr[j] = r;
+        const T z = r * idg[j];
+        pv[j] = z;
+        ps[li[j]] = z;
+        const double bd = has ? (double)q.bb : 0.0;
+        rz += (double)r * (double)z;
+        r2 += (double)r * (double)r;
+        b2 += bd * bd;
       }
-      dg[j] = q.d;
-      idg[j] = q.d > (T)0 ? (T)1 / q.d : (T)0;   // d = 0 only without network and gradient terms
-      cR[j] = q.cr; cL[j] = q.cl; cD[j] = q.cd; cU[j] = q.cu;
-      const T ax = q.d * xi - q.cr * xR - q.cl * xL - q.cd * xD - q.cu * xU;
-      const T r = q.bb - ax;
-      rr[j] = r;
-      const T z = r * idg[j];
-      pv[j] = z;
-      ps[l] = z;
-      rz += (double)r * (double)z;
-      r2 += (double)r * (double)r;
-      b2 += (double)q.bb * (double)q.bb;
+      __builtin_amdgcn_sched_barrier(0);
     }
     int it = 0;
     T qv[PPT];
@@ -784,13 +834,12 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
 #pragma unroll
       for (int j = 0; j < PPT; ++j) {
         uv[j] = pv[j];
-        wv[j] = mv[j] = zv[j] = sv[j] = qv[j] = (T)0;
-        if (lxy[j] < 0) continue;
-        const int l = KF_LI(j);
+        zv[j] = sv[j] = qv[j] = (T)0;
+        const int l = li[j];
         const T w = dg[j] * uv[j] - cR[j] * ps[l + 1] - cL[j] * ps[l - 1] - cD[j] * ps[l + rw] - cU[j] * ps[l - rw];
         wv[j] = w;
         mv[j] = w * idg[j];
-        ms0[l] = mv[j];
+        ms0[li[j]] = mv[j];
       }
       // alpha_i = gamma_i / (delta_i - beta_i gamma_i / alpha_{i-1}); with
       // den_i = gamma_i / alpha_i the last term is beta_i^2 den_{i-1}, so only
@@ -801,35 +850,16 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
         T* mring = (i & 1) ? ps : ms0;
         T* mnext = (i & 1) ? ms0 : ps;
 #pragma unroll
-        for (int j = 0; j < PPT; ++j) refresh(lxy[j]);
+        for (int j = 0; j < PPT; ++j) refresh(li[j]);
         double ga = 0.0, de = 0.0;
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
-          if (lxy[j] < 0) continue;
           ga += (double)rr[j] * (double)uv[j];
           de += (double)wv[j] * (double)uv[j];
         }
         vals[0] = ga; vals[1] = de;
-        // the stencil product of the tile's interior pixels needs no ghost
-        // value: it is formed while the team's words are in flight (for up to
-        // 4 pixels per thread; with more, the extra registers cost more than
-        // the overlap gains)
-        constexpr bool OVERLAP = PPT <= 4;
-        T nint[PPT];
-        auto interior = [&] {
-#pragma unroll
-          for (int j = 0; j < PPT; ++j) {
-            nint[j] = (T)0;
-            if (!OVERLAP || lxy[j] < 0) continue;
-            const int lx = KF_LX(j), ly = KF_LY(j);
-            if (lx == 0 || ly == 0 || lx == tw - 1 || ly == th - 1) continue;
-            const int l = KF_LI(j);
-            nint[j] = dg[j] * mv[j] - cR[j] * mring[l + 1] - cL[j] * mring[l - 1] - cD[j] * mring[l + rw] -
-                      cU[j] * mring[l - rw];
-          }
-        };
         // the neighbours' m lands directly in the ghost ring of mring
-        if (!tm.template sync<false>(e++, 2, vals, tot, gval, true, mring, true, interior)) return;
+        if (!tm.sync(e++, 2, vals, tot, gval, true, mring, true)) return;
         if (tot[0] == 0.0) break;
         double beta = 0.0, den = tot[1];
         if (i > 0) {
@@ -840,19 +870,24 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
         rgamma_prev = 1.0 / tot[0];
         den_prev = den;
         const T al = (T)alpha, be = (T)beta;
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) refresh(li[j]);   // (addresses kept over the wait would take registers)
         const bool last = i == limit - 1;
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
-          if (lxy[j] < 0) continue;
           pv[j] = i > 0 ? fma(be, pv[j], uv[j]) : uv[j];
           xr[j] = fma(al, pv[j], xr[j]);
-          if (last) continue;
-          const int l = KF_LI(j);
-          const int lx = KF_LX(j), ly = KF_LY(j);
-          T n = nint[j];
-          if (!OVERLAP || lx == 0 || ly == 0 || lx == tw - 1 || ly == th - 1)
-            n = dg[j] * mv[j] - cR[j] * mring[l + 1] - cL[j] * mring[l - 1] - cD[j] * mring[l + rw] -
-                cU[j] * mring[l - rw];
+        }
+        if (last) {
+          ++it;
+          break;
+        }
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+          const int l = li[j];
+          const T n = fma(-cU[j], mring[l - rw],
+                          fma(-cD[j], mring[l + rw],
+                              fma(-cL[j], mring[l - 1], fma(dg[j], mv[j], -rounded(cR[j] * mring[l + 1])))));
           zv[j] = i > 0 ? fma(be, zv[j], n) : n;
           qv[j] = i > 0 ? fma(be, qv[j], mv[j]) : mv[j];
           sv[j] = i > 0 ? fma(be, sv[j], wv[j]) : wv[j];
@@ -860,7 +895,7 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
           uv[j] = fma(-al, qv[j], uv[j]);
           wv[j] = fma(-al, zv[j], wv[j]);
           mv[j] = wv[j] * idg[j];
-          mnext[l] = mv[j];
+          mnext[li[j]] = mv[j];
         }
         ++it;
       }
@@ -868,13 +903,11 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
     while (!PIPE && !converged && it < limit && rz_t != 0.0) {
       // q = A p (5-point stencil; ghost ring holds the neighbours' p)
 #pragma unroll
-      for (int j = 0; j < PPT; ++j) refresh(lxy[j]);
+      for (int j = 0; j < PPT; ++j) refresh(li[j]);
       double pq = 0.0;
 #pragma unroll
       for (int j = 0; j < PPT; ++j) {
-        qv[j] = (T)0;
-        if (lxy[j] < 0) continue;
-        const int l = KF_LI(j);
+        const int l = li[j];
         const T q = dg[j] * pv[j] - cR[j] * ps[l + 1] - cL[j] * ps[l - 1] - cD[j] * ps[l + rw] - cU[j] * ps[l - rw];
         qv[j] = q;
         pq += (double)pv[j] * (double)q;
@@ -886,7 +919,6 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
       double rzn = 0.0, rrn = 0.0;
 #pragma unroll
       for (int j = 0; j < PPT; ++j) {
-        if (lxy[j] < 0) continue;
         xr[j] += al * pv[j];
         rr[j] -= al * qv[j];
         const T z = rr[j] * idg[j];
@@ -898,7 +930,7 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
       if (!tol_mode && it == limit) break;
 #pragma unroll
       for (int j = 0; j < PPT; ++j)
-        if (lxy[j] >= 0) tm.publish(e, KF_LX(j), KF_LY(j), qv[j]);
+        if (li[j] > 0) tm.publish(e, KF_U(j) - ox, KF_V(j) - oy, qv[j]);
       vals[0] = rzn; vals[1] = rrn;
       // ghost z arrives in gval: the ghost copy of p needs beta first
       if (!tm.sync(e++, tol_mode ? 2 : 1, vals, tot, gval, true)) return;
@@ -913,9 +945,8 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
       rz_t = tot[0];
 #pragma unroll
       for (int j = 0; j < PPT; ++j) {
-        if (lxy[j] < 0) continue;
         pv[j] = fma(be, pv[j], qv[j]);
-        ps[KF_LI(j)] = pv[j];
+        ps[li[j]] = pv[j];
       }
 #pragma unroll
       for (int m = 0; m < GMAX; ++m)
@@ -927,20 +958,17 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
 
     // ---- scale step: semi weights at (x_new, tau), tau = sum w (x - z) / sum w (R13)
 #pragma unroll
-    for (int j = 0; j < PPT; ++j) refresh(lxy[j]);
+    for (int j = 0; j < PPT; ++j) refresh(li[j]);
     double num = 0.0, den = 0.0, cnt = 0.0;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-      if (lxy[j] < 0) continue;
       T zs;
-      const T isr = semi(KF_GI(j), zs);
-      if (isr > (T)0) {
-        const T w = huber_w((xr[j] - (T)tau - zs) * isr, delta, tukey) * isr * isr;
-        num += (double)w * (double)(xr[j] - zs);
-        den += (double)w;
-        cnt += 1.0;
-      }
-      xs[KF_LI(j)] = xr[j];
+      const T isr = semi_own(j, zs);   // 0: no measurement, weight 0
+      const T w = huber_w((xr[j] - (T)tau - zs) * isr, delta, tukey) * isr * isr;
+      num += (double)w * (double)(xr[j] - zs);
+      den += (double)w;
+      cnt += isr > (T)0 ? 1.0 : 0.0;
+      if (li[j] > 0) xs[li[j]] = xr[j];
     }
     vals[0] = num; vals[1] = den; vals[2] = cnt;
     // the neighbours' x lands directly in the ghost ring of xs (with
@@ -965,8 +993,8 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
     double dev = 0.0;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-      refresh(lxy[j]);
-      if (lxy[j] >= 0) dev += (double)mu_g[KF_GI(j)] - (double)xr[j];
+      refresh(li[j]);
+      if (li[j] > 0) dev += (double)mu_g[KF_GI(j)] - (double)xr[j];
     }
     vals[0] = dev;
     if (!tm.sync(e++, 1, vals, tot, gval, false)) return;
@@ -977,10 +1005,10 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
 
 #pragma unroll
   for (int j = 0; j < PPT; ++j)
-    if (lxy[j] >= 0 && !new_kf) x_g[KF_GI(j)] = xr[j];
-#undef KF_LX
-#undef KF_LY
-#undef KF_LI
+    if (li[j] > 0 && !new_kf) x_g[KF_GI(j)] = xr[j];
+#undef KF_ROW
+#undef KF_U
+#undef KF_V
 #undef KF_GI
   if (b == 0 && tid == 0) {
     // every member has read e0 before its first publish, and workgroup 0
@@ -1071,10 +1099,15 @@ namespace {
     KF_PPT(1024, 3)                                                                   \
   }
 
-size_t smem_for(size_t elt, const Tiling& t) {
+size_t smem_base(size_t elt, const Tiling& t) {
   const size_t ring = (size_t)(t.tile_h + 2) * (t.tile_w + 2);
   const size_t ring2 = 2 * (size_t)t.tile_w + 2 * (size_t)t.tile_h;
   return sizeof(double) * ((size_t)(t.threads / 64) * NV_MAX + NV_MAX * (MAX_TEAM / 64) + 2) + (3 * ring + 13 * ring2) * elt;
+}
+size_t smem_keep(size_t elt, const Tiling& t) { return 2 * (size_t)t.tile_w * t.tile_h * elt; }
+
+size_t smem_for(size_t elt, const Tiling& t) {
+  return smem_base(elt, t) + (solve_keeps(elt, t) ? smem_keep(elt, t) : 0);
 }
 
 template <typename T, bool PIPE, bool VAR>
@@ -1130,6 +1163,13 @@ const void* batch_kernel_of(const SolveKernel& k) {
 }
 
 }  // namespace
+
+// Whether the LDS also holds the own pixels' semi-dense measurements: where that
+// leaves as many workgroups on a compute unit (160 KiB) as there would be without.
+bool solve_keeps(size_t elt, const Tiling& t) {
+  const size_t base = smem_base(elt, t), all = base + smem_keep(elt, t), cu = 160 * 1024;
+  return cu / all == cu / base || (all <= cu && cu / all >= (size_t)(1024 / t.threads));
+}
 
 size_t solve_smem_bytes(int prec, const Tiling& t) {
   return t.s ? sstep_smem_bytes(t) : smem_for(prec == KF_F64 ? 8 : 4, t);

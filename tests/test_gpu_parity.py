@@ -412,6 +412,29 @@ def test_frame_pipelining_gives_the_same_results(c1_short):
     assert a["tau"] == b["tau"] and (ua, va) == (ub, vb)
 
 
+def _random_state_solve(W, H, tiles, n_cg, threads=0):
+    """3 GN iterations in float32 from a seeded random state; returns the context
+    and the deviations of x and tau from the oracle's iteration-matched solve."""
+    rng = np.random.default_rng(W * 1000 + H)
+    prior = PriorMaps(rng.normal(0.5, 0.3, (H, W)), rng.uniform(0.01, 0.2, (H, W)), rng.normal(0, 0.05, (H, W)),
+                      rng.uniform(1e-3, 1e-2, (H, W)), rng.normal(0, 0.05, (H, W)), rng.uniform(1e-3, 1e-2, (H, W)))
+    has = rng.random((H, W)) < 0.3
+    rho = np.where(has, rng.uniform(0.3, 1.2, (H, W)), 0.0).astype(np.float32)
+    var = np.where(has, rng.uniform(1e-4, 1e-2, (H, W)), 0.0).astype(np.float32)
+    from paper_2207_12244_amd.kf import Keyframe
+    t = gu.torch()
+    K = np.array([[0.8 * W, 0.0, W / 2.0], [0.0, 0.8 * W, H / 2.0], [0.0, 0.0, 1.0]])
+    kf = Keyframe(W, H, precision="f32", n_gn=3, n_cg=n_cg, K=K, tiles=tiles, solver_threads=threads)
+    kf.set_prior(gu.dev(np.zeros((H, W)), t.uint8), *[gu.dev(m, t.float32) for m in vars(prior).values()], np.eye(4))
+    kf.import_state(rho=gu.dev(rho, t.float32), var=gu.dev(var, t.float32))
+    kf.solve()
+    st = kf.export_state()
+    maps = PriorMaps(*[np.asarray(m, np.float32).astype(np.float64) for m in vars(prior).values()])
+    x_o, tau_o, _ = fusion.gauss_newton(maps.mu, 0.0, maps, gu.oracle_semi(rho.astype(np.float64), var.astype(np.float64)),
+                                        SolverParams(n_gn=3, n_cg=n_cg, linear_solver="pcg"))
+    return kf, np.abs(st["x"].cpu().numpy().astype(np.float64) - x_o), abs(st["tau"] - tau_o)
+
+
 @pytest.mark.parametrize("W,H,tiles,n_cg,syncs", [
     (8, 8, (1, 1), 100, None),       # more iterations than unknowns: CG converges and ends early
     (16, 16, (1, 1), 3, 1),          # 1 row per thread, one block of fewer iterations than it could make
@@ -435,26 +458,19 @@ def test_solver_sstep_shapes(W, H, tiles, n_cg, syncs):
     early. Tolerance: that of the other float solves (x of order 1 through at
     most 3 x 20 float32 iterations)."""
     gu.say(f"[solver-sstep] {W}x{H} tiles {tiles} n_cg {n_cg}")
-    rng = np.random.default_rng(W * 1000 + H)
-    prior = PriorMaps(rng.normal(0.5, 0.3, (H, W)), rng.uniform(0.01, 0.2, (H, W)), rng.normal(0, 0.05, (H, W)),
-                      rng.uniform(1e-3, 1e-2, (H, W)), rng.normal(0, 0.05, (H, W)), rng.uniform(1e-3, 1e-2, (H, W)))
-    has = rng.random((H, W)) < 0.3
-    rho = np.where(has, rng.uniform(0.3, 1.2, (H, W)), 0.0).astype(np.float32)
-    var = np.where(has, rng.uniform(1e-4, 1e-2, (H, W)), 0.0).astype(np.float32)
-    from paper_2207_12244_amd.kf import Keyframe
-    t = gu.torch()
-    K = np.array([[0.8 * W, 0.0, W / 2.0], [0.0, 0.8 * W, H / 2.0], [0.0, 0.0, 1.0]])
-    kf = Keyframe(W, H, precision="f32", n_gn=3, n_cg=n_cg, K=K, tiles=tiles)
-    kf.set_prior(gu.dev(np.zeros((H, W)), t.uint8), *[gu.dev(m, t.float32) for m in vars(prior).values()], np.eye(4))
-    kf.import_state(rho=gu.dev(rho, t.float32), var=gu.dev(var, t.float32))
-    kf.solve()
-    st = kf.export_state()
-    maps = PriorMaps(*[np.asarray(m, np.float32).astype(np.float64) for m in vars(prior).values()])
-    x_o, tau_o, _ = fusion.gauss_newton(maps.mu, 0.0, maps, gu.oracle_semi(rho.astype(np.float64), var.astype(np.float64)),
-                                        SolverParams(n_gn=3, n_cg=n_cg, linear_solver="pcg"))
-    err = np.abs(st["x"].cpu().numpy().astype(np.float64) - x_o)
+    kf, err, dtau = _random_state_solve(W, H, tiles, n_cg)
     gu.say(f"[solver-sstep] max|dx| {err.max():.3e} rms {np.sqrt(np.mean(err ** 2)):.3e} "
-           f"dtau {abs(st['tau'] - tau_o):.3e} syncs {kf.stats().team_syncs}")
+           f"dtau {dtau:.3e} syncs {kf.stats().team_syncs}")
     if syncs is not None:
         assert kf.stats().team_syncs == 3 * (syncs + 1)   # per GN iteration: the blocks and the scale step
-    assert err.max() <= 2e-4 and np.sqrt(np.mean(err ** 2)) <= 2e-5 and abs(st["tau"] - tau_o) <= 2e-5
+    assert err.max() <= 2e-4 and np.sqrt(np.mean(err ** 2)) <= 2e-5 and dtau <= 2e-5
+
+
+@pytest.mark.parametrize("W,H", [(500, 10), (72, 70), (17, 9)])
+def test_solver_one_tile_shapes(W, H):
+    """One workgroup of 512 threads with an explicit workgroup size: a tile too
+    long for the semi-dense measurements to stay in LDS, one where they do, and
+    one with fewer pixels than threads. Tolerance as for the s-step shapes."""
+    kf, err, dtau = _random_state_solve(W, H, (1, 1), 15, threads=512)
+    gu.say(f"[solver-one-tile] {W}x{H} max|dx| {err.max():.3e} dtau {dtau:.3e}")
+    assert err.max() <= 2e-4 and np.sqrt(np.mean(err ** 2)) <= 2e-5 and dtau <= 2e-5
