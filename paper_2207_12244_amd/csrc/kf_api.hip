@@ -684,7 +684,9 @@ kf_status set_prior_impl(kf_ctx* c, const uint8_t* image0, const void* const map
   std::memcpy(c->T_wc0, T_wc0, sizeof(c->T_wc0));
   // exchange words and device scalars start from zero (epoch 0 is never used)
   hipError_t e = wait_solves(c);
-  if (e == hipSuccess) e = launch_zero(c->ws + c->lay.scal, c->lay.total - c->lay.scal, c->stream);
+  // the words that carry tags start at zero; the s-step solver's pixel data has none
+  const size_t tagged_end = c->tiling.s ? c->lay.halo : c->lay.total;
+  if (e == hipSuccess) e = launch_zero(c->ws + c->lay.scal, tagged_end - c->lay.scal, c->stream);
   if (e == hipSuccess && c->lay.match > c->lay.rho2)   // second filter-state buffer
     e = launch_zero(c->ws + c->lay.rho2, c->lay.match - c->lay.rho2, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "kf_set_prior (clear)");

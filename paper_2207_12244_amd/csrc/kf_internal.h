@@ -142,7 +142,7 @@ struct PriorArgs {
   void* i0;                  // TI[N]
   void* prior;               // T[6][N]: mu, isd_n, gx, isd_gx, gy, isd_gy (isd = 1/sigma)
   void* x; void* rho; void* var; int32_t* match;
-  int32_t* chunk_counts;     // [nchunks + 1]
+  int32_t* chunk_counts;     // [nchunks]
   int32_t* list;             // [N]
   DevScalars* scal;
   double grad_gate;

@@ -95,37 +95,12 @@ __global__ __launch_bounds__(256) void k_resample_priors(ResampleArgs r) {
   }
 }
 
-// Exclusive scan of the per-chunk counts (one workgroup), total -> mask_count.
-__global__ __launch_bounds__(1024) void k_scan_chunks(int32_t* counts, int nchunks, DevScalars* scal) {
-  __shared__ int32_t part[1024];
-  __shared__ int32_t carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int base = 0; base < nchunks; base += 1024) {
-    const int c = base + threadIdx.x;
-    const int32_t v = c < nchunks ? counts[c] : 0;
-    part[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-      int32_t t = threadIdx.x >= off ? part[threadIdx.x - off] : 0;
-      __syncthreads();
-      part[threadIdx.x] += t;
-      __syncthreads();
-    }
-    if (c < nchunks) counts[c] = carry + part[threadIdx.x] - v;
-    __syncthreads();
-    if (threadIdx.x == 1023) carry += part[1023];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    counts[nchunks] = carry;
-    scal->mask_count = carry;
-  }
-}
-
-// Writes the textured pixels, in row-major order, into the search list.
+// Writes the textured pixels, in row-major order, into the search list. Every
+// workgroup adds the chunk counts before its own (from L2: 4.8 KB at 640 x 480,
+// 20 KB at 1280 x 1024, about the largest keyframe). A launch that scanned them
+// first took a new prior from 20.4 to 21.9 us and from 29.4 to 34.5.
 __global__ __launch_bounds__(CHUNK) void k_write_list(PriorArgs a) {
-  __shared__ int32_t wave_cnt[CHUNK / 64];
+  __shared__ int32_t wave_cnt[CHUNK / 64], wave_sum[CHUNK / 64];
   const int N = a.W * a.H;
   const int i = blockIdx.x * CHUNK + threadIdx.x;
   bool m = false;
@@ -135,8 +110,14 @@ __global__ __launch_bounds__(CHUNK) void k_write_list(PriorArgs a) {
   const uint64_t below = lane ? (ballot & ((~0ull) >> (64 - lane))) : 0ull;
   const int rank = __popcll(below);
   if (lane == 0) wave_cnt[wave] = __popcll(ballot);
+  int s = 0;
+  for (int c = threadIdx.x; c < (int)blockIdx.x; c += CHUNK) s += a.chunk_counts[c];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (lane == 0) wave_sum[wave] = s;
   __syncthreads();
-  int off = a.chunk_counts[blockIdx.x];
+  int off = 0;
+  for (int w = 0; w < CHUNK / 64; ++w) off += wave_sum[w];
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) a.scal->mask_count = off + a.chunk_counts[blockIdx.x];
   for (int w = 0; w < wave; ++w) off += wave_cnt[w];
   if (m) a.list[off + rank] = i;
 }
@@ -178,7 +159,6 @@ hipError_t prior_impl(const PriorArgs& a, hipStream_t s) {
   const int N = a.W * a.H;
   const int nchunks = (N + CHUNK - 1) / CHUNK;
   hipLaunchKernelGGL((k_prior_init<T, TI>), dim3(nchunks), dim3(CHUNK), 0, s, a);
-  hipLaunchKernelGGL(k_scan_chunks, dim3(1), dim3(1024), 0, s, a.chunk_counts, nchunks, a.scal);
   hipLaunchKernelGGL(k_write_list, dim3(nchunks), dim3(CHUNK), 0, s, a);
   return hipGetLastError();
 }

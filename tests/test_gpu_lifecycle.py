@@ -105,3 +105,29 @@ def test_rule_per_member_in_a_batch():
         else:
             assert s.new_keyframe == 0 and not np.array_equal(st["x"], c.priors.logdepth.astype(np.float32))
     batch.close()
+
+
+@pytest.mark.parametrize("W,H", [(8, 8), (16, 16), (257, 9), (129, 131), (1280, 1024)])
+def test_search_list_counts(W, H):
+    """The search list at the edges of its chunks of 256 pixels (fewer than one,
+    exactly one, a remainder) and at the largest keyframe: as many pixels as the
+    oracle's texture mask has, and measurements at those pixels alone."""
+    from oracle import stereo
+    from paper_2207_12244_amd.kf import Keyframe
+    t = gu.torch()
+    rng = np.random.default_rng(W * 10000 + H)
+    img = rng.integers(0, 256, (H, W)).astype(np.uint8)
+    img[: H // 2, : W // 3] = 128   # flat: not searched
+    mask = stereo.texture_mask(img)
+    K = np.array([[0.8 * W, 0.0, W / 2.0], [0.0, 0.8 * W, H / 2.0], [0.0, 0.0, 1.0]])
+    kf = Keyframe(W, H, precision="f32", pattern="line5", n_samples=4, K=K)
+    one = np.ones((H, W))
+    kf.set_prior(gu.dev(img, t.uint8), *[gu.dev(m, t.float32) for m in (0 * one, one, 0 * one, one, 0 * one, one)],
+                 np.eye(4))
+    pose = np.eye(4)
+    pose[0, 3] = 0.05
+    kf.stereo_update(gu.dev(img, t.uint8), pose)
+    assert kf.stats().n_searched == int(mask.sum())
+    match = kf.export_state()["match"].cpu().numpy()
+    assert np.array_equal(match == -2, ~mask)
+    kf.close()
