@@ -782,8 +782,12 @@ kf_status kf_stereo_update(kf_ctx* c, const uint8_t* image1, const double T_wc1[
   }
   // beside a solve still in flight the update takes one workgroup per compute
   // unit; with none in flight (the user stream waited for them all) the
-  // resident grid
-  const bool beside = c->cfg.pipeline_frames && !c->solves_waited;
+  // resident grid. The s-step solver's workgroups leave no registers for the
+  // update on their compute units, so it runs on the others and, mostly, after
+  // the solve: the resident grid too (640 x 480, 30 frames pipelined: 14.0 ms
+  // with one workgroup per unit, 12.8 with two, 12.3 with three, the resident
+  // number, 12.7 with six; 320 x 240: 8.1 with any)
+  const bool beside = c->cfg.pipeline_frames && !c->solves_waited && !c->tiling.s;
   if (e == hipSuccess) e = launch_stereo(c->cfg.precision, c->cfg.pattern, c->cfg.n_samples, a, c->cus, beside, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "kf_stereo_update");
   if (c->cfg.pipeline_frames) c->cur = nxt;
