@@ -36,7 +36,13 @@
  *     that the next synchronising call returns (KF_ERR_INPUT, KF_ERR_TIMEOUT).
  *     kf_last_error gives a message for the last failure on the context.
  *   - Threading: a context is externally synchronised; distinct contexts are
- *     independent (each has its own workspace).
+ *     independent (each has its own workspace), on the same or on different
+ *     streams and threads of one process. The workgroups of a solve wait for each
+ *     other, so solves on different streams that might not all fit on the device
+ *     run one after the other: the later one's stream waits for the earlier one's.
+ *     (Many keyframes at once are the batched form's case.) Not seen, and so for
+ *     the caller to order: solves that a captured graph replays, that a stream
+ *     has not ended when its capture begins, and those of other processes. A context's stream must outlive it.
  */
 #ifndef KF_H
 #define KF_H

@@ -21,7 +21,7 @@ LIB = os.path.join(PKG, "libkf.so")
 ARCH = os.environ.get("KF_OFFLOAD_ARCH", "gfx950")
 
 SOURCES = ["kf_sstep_batch.hip", "kf_sstep4.hip", "kf_sstep2.hip", "kf_solve.hip", "kf_stereo.hip",
-           "kf_api.hip", "kf_batch.hip", "kf_prior.hip"]
+           "kf_api.hip", "kf_admit.hip", "kf_batch.hip", "kf_prior.hip"]
 
 COMMON = [
     f"--offload-arch={ARCH}",

@@ -1,0 +1,85 @@
+// The admission of solver launches (kf_admit.h) over HIP streams and events.
+#include "kf_admit.h"
+
+#include "kf_internal.h"
+
+namespace kf {
+
+namespace {
+
+// Calls on other streams than a captured one are legal, but a capture in global
+// mode of some other thread objects to an event query unless this one is relaxed.
+struct Relaxed {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  bool on;
+  Relaxed() : on(hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {}
+  ~Relaxed() {
+    if (on) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+};
+
+bool good(hipError_t e) {
+  if (e == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
+struct HipOps {
+  using Stream = hipStream_t;
+  using Event = hipEvent_t;
+  int device;
+  // orders work of this device only, so without the system-scope fence
+  bool create(Event& e) const {
+    int cur = -1;
+    if (!good(hipGetDevice(&cur)) || (cur != device && !good(hipSetDevice(device)))) return false;
+    const bool made = good(hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventDisableSystemFence));
+    if (cur != device) (void)good(hipSetDevice(cur));
+    return made;
+  }
+  void destroy(Event& e) const { (void)good(hipEventDestroy(e)); }
+  bool record(Event& e, Stream s) const { return !capturing(s) && good(hipEventRecord(e, s)); }
+  bool done(Event& e) const {
+    Relaxed relaxed;
+    const hipError_t r = hipEventQuery(e);
+    if (r == hipErrorNotReady) (void)hipGetLastError();
+    return r != hipErrorNotReady;
+  }
+  bool wait(Stream s, Event& e) const { return good(hipStreamWaitEvent(s, e, 0)); }
+  // (a per-thread default stream is another one in every thread)
+  bool same(Stream a, Stream b) const { return a == b && a != hipStreamPerThread; }
+  bool capturing(Stream s) const {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return !good(hipStreamIsCapturing(s, &st)) || st != hipStreamCaptureStatusNone;
+  }
+};
+
+using Device = Admission<HipOps>;
+
+// One per device for the life of the process (contexts may outlive static objects).
+Device* admission_of(int device) {
+  constexpr int MAX_DEVICES = 64;
+  static std::mutex mu;
+  static Device* all[MAX_DEVICES] = {};
+  if (device < 0 || device >= MAX_DEVICES) return nullptr;
+  std::lock_guard<std::mutex> lock(mu);
+  if (!all[device]) all[device] = new (std::nothrow) Device(device_cus(device), HipOps{device});
+  return all[device];
+}
+
+}  // namespace
+
+hipError_t admit_launch(kf_ctx* c, hipStream_t s, int blocks, int coresident, hipError_t (*go)(void*), void* arg) {
+  Device* d = admission_of(c->device);
+  if (d && !c->lane) c->lane = d->join(s);
+  if (!c->lane) return hipErrorOutOfMemory;
+  const int per_cu = coresident / c->cus;
+  return d->launch(static_cast<Device::Lane*>(c->lane), blocks, per_cu, hipSuccess, hipErrorInvalidHandle,
+                   [&] { return go(arg); });
+}
+
+void admit_leave(kf_ctx* c) {
+  if (c->lane) admission_of(c->device)->leave(static_cast<Device::Lane*>(c->lane));
+  c->lane = nullptr;
+}
+
+}  // namespace kf

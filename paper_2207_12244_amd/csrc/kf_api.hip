@@ -647,6 +647,7 @@ kf_status kf_create(const kf_config* cfg, kf_ctx** out) {
 void kf_destroy(kf_ctx* ctx) {
   if (!ctx) return;
   if (ctx->solve_stream) (void)hipStreamSynchronize(ctx->solve_stream);
+  admit_leave(ctx);
   for (hipEvent_t ev : ctx->ev_solve)
     if (ev) (void)hipEventDestroy(ev);
   if (ctx->ev_user) (void)hipEventDestroy(ctx->ev_user);
@@ -821,7 +822,8 @@ kf_status kf_solve(kf_ctx* c) {
     if (e == hipSuccess) e = hipStreamWaitEvent(s, c->ev_user, 0);
     if (e != hipSuccess) return hip_fail(c, e, "kf_solve (ordering)");
   }
-  e = launch_solve(g.precision, c->tiling, a, g.solver_cooperative != 0, kind, s);
+  e = admitted(c, s, c->tiling.blocks, c->coresident,
+               [&] { return launch_solve(g.precision, c->tiling, a, g.solver_cooperative != 0, kind, s); });
   if (e == hipSuccess && g.pipeline_frames) {
     e = hipEventRecord(c->ev_solve[c->cur], s);
     c->solve_pending[c->cur] = true;
@@ -923,7 +925,8 @@ kf_status kf_fuse_frame_static(kf_ctx* c, const uint8_t* image1, const double T_
   if (c->coresident < c->tiling.blocks)
     return fail(c, KF_ERR_ARG, "solver tiling needs " + std::to_string(c->tiling.blocks) +
                                " co-resident workgroups, the device holds " + std::to_string(c->coresident));
-  e = launch_solve(g.precision, c->tiling, sa, g.solver_cooperative != 0, kind, c->stream);
+  e = admitted(c, c->stream, c->tiling.blocks, c->coresident,
+               [&] { return launch_solve(g.precision, c->tiling, sa, g.solver_cooperative != 0, kind, c->stream); });
   if (e != hipSuccess) return hip_fail(c, e, "kf_fuse_frame_static (solve)");
   c->epoch += bound;
   return KF_OK;
@@ -944,7 +947,8 @@ kf_status kf_probe_sync(kf_ctx* c, int32_t rounds, int32_t nvalues) {
   a.packed = (c->cfg.precision != KF_F64 && bound < 30000) ? 1 : 0;
   if (c->coresident < 0) c->coresident = solve_max_coresident(c->cfg.precision, c->tiling, solve_kind(c->cfg), c->device);
   if (c->coresident < c->tiling.blocks) return fail(c, KF_ERR_ARG, "kf_probe_sync: tiling not co-resident");
-  e = launch_sync_probe(c->cfg.precision, c->tiling, a, rounds, nvalues, c->stream);
+  e = admitted(c, c->stream, c->tiling.blocks, c->coresident,
+               [&] { return launch_sync_probe(c->cfg.precision, c->tiling, a, rounds, nvalues, c->stream); });
   if (e != hipSuccess) return hip_fail(c, e, "kf_probe_sync");
   c->epoch += bound;
   return KF_OK;

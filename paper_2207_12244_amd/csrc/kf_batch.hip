@@ -52,6 +52,7 @@ struct Family {
   SolveKernel k{};
   size_t smem = 0;
   int grid = 0;                    // workgroups; 0: no member of this family
+  int capacity = 0;                // of them that the device holds at once
   int max_queue = 0;               // longest per-workgroup queue of the last schedule
   std::vector<int32_t> queue, qoff;
 };
@@ -258,11 +259,18 @@ kf_status run_call(kf_batch* b, int which, const std::vector<int>& active, const
   if (e != hipSuccess) return bhip(b, e, std::string(who) + " (descriptor upload)");
   b->ev_used[p] = true;
   b->parity ^= 1;
-  if (b->use_graph) {
-    e = graph_for(b, which);
-    if (e == hipSuccess) e = hipGraphLaunch(b->exec[which], b->stream);
-  } else {
-    e = enqueue(b, which, b->stream);
+  if (b->use_graph) e = graph_for(b, which);
+  auto go = [&] { return b->use_graph ? hipGraphLaunch(b->exec[which], b->stream) : enqueue(b, which, b->stream); };
+  if (e == hipSuccess && solve) {
+    int blocks = 0, coresident = 0;
+    for (const Family& fam : b->fam) {
+      if (!fam.grid) continue;
+      blocks = std::max(blocks, fam.grid);
+      coresident = coresident ? std::min(coresident, fam.capacity) : fam.capacity;
+    }
+    e = admitted(b->m[0], b->stream, blocks, coresident, go);
+  } else if (e == hipSuccess) {
+    e = go();
   }
   if (e != hipSuccess) return bhip(b, e, who);
   for (int i : active) {
@@ -363,6 +371,7 @@ kf_status kf_batch_create(kf_ctx* const* members, int32_t n, const kf_batch_conf
       return KF_ERR_ARG;
     }
     fam.grid = std::min(capacity, blocks[f]);
+    fam.capacity = capacity;
     schedule(b, f, everyone);
     full_queue = std::max(full_queue, fam.max_queue);
   }

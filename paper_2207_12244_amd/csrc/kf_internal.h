@@ -267,6 +267,16 @@ __host__ __device__ inline int sstep_frame_words(int tile_w, int tile_h, int s) 
 }
 // Compute units of the device (256 if the query fails).
 int device_cus(int device);
+// Launches a solver team of c's by go(arg) on stream s (always the same one of a
+// context), ordered behind the launches of other streams that it could not be
+// resident with. coresident: workgroups of its kernel that the device holds.
+hipError_t admit_launch(kf_ctx* c, hipStream_t s, int blocks, int coresident, hipError_t (*go)(void*), void* arg);
+template <typename F>
+hipError_t admitted(kf_ctx* c, hipStream_t s, int blocks, int coresident, const F& go) {
+  return admit_launch(c, s, blocks, coresident, [](void* f) { return (*static_cast<const F*>(f))(); },
+                      const_cast<F*>(&go));
+}
+void admit_leave(kf_ctx* c);   // before the stream goes
 
 }  // namespace kf
 
@@ -296,6 +306,7 @@ struct kf_ctx {
   bool solve_pending[2] = {false, false};
   int last_solve = -1;                    // buffer of the last enqueued solve
   bool solves_waited = true;              // the user stream waits for every enqueued solve
+  void* lane = nullptr;                   // of the solves' stream (kf_admit.h), from the first solve on
 };
 
 namespace kf {

@@ -131,3 +131,50 @@ def test_search_list_counts(W, H):
     match = kf.export_state()["match"].cpu().numpy()
     assert np.array_equal(match == -2, ~mask)
     kf.close()
+
+
+@pytest.mark.parametrize("pipelined", [False, True])
+def test_contexts_on_different_streams(pipelined):
+    """Three keyframes whose solver teams do not fit on the device together, each
+    on a stream of its own and enqueued without a wait: the results of the same
+    calls one after the other, and no team times out. A batch on a fourth stream
+    runs in between."""
+    from paper_2207_12244_amd.kf import Batch, Keyframe
+    t = gu.torch()
+    cases = [kfsynth.config_case(3, 20 + i, size_index=s, frames=8) for i, s in enumerate((3, 3, 2, 1, 1))]
+
+    def make(c, stream, **kw):
+        kf = Keyframe(c.W, c.H, precision="f32", n_samples=32, K=c.K, stream=stream, **kw)
+        maps = [gu.dev(c.image0, t.uint8), *[gu.dev(m, t.float32) for m in c.priors.maps()]]
+        t.cuda.synchronize()
+        kf.set_prior(*maps, c.T_wc0)
+        return kf
+
+    images = [[gu.dev(im, t.uint8) for im in c.images] for c in cases]
+
+    def run(streams, wait):
+        kfs = [make(c, s, pipeline_frames=pipelined and i < 3) for i, (c, s) in enumerate(zip(cases, streams))]
+        batch = Batch(kfs[3:])
+        t.cuda.synchronize()
+        for f in range(8):
+            for i in range(3):
+                kfs[i].fuse_frame(images[i][f], cases[i].poses[f])
+                if wait:
+                    t.cuda.synchronize()
+            batch.fuse([images[i][f] for i in (3, 4)], [cases[i].poses[f] for i in (3, 4)])
+            if wait:
+                t.cuda.synchronize()
+        t.cuda.synchronize()
+        states = [gu.np_state(kf) for kf in kfs]
+        batch.close()
+        for kf in kfs:
+            kf.close()
+        return states
+
+    own = [t.cuda.Stream() for _ in range(4)]
+    alone = run([t.cuda.current_stream()] * 5, True)
+    mixed = run(own + own[3:], False)
+    for i, (a, b) in enumerate(zip(alone, mixed)):
+        for k in ("x", "rho", "var", "match"):
+            assert np.array_equal(a[k], b[k]), (i, k)
+        assert a["tau"] == b["tau"], i
