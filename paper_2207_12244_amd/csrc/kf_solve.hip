@@ -1027,8 +1027,30 @@ __device__ __forceinline__ void solve_member(const SolveArgs& a, const int b, un
   }
 }
 
+// Wavefronts per SIMD that an instance's registers have to leave room for (1: as
+// many as they come to). A batch runs as many workgroups as the device holds, so
+// an instance a few registers past a step runs fewer teams at once (8 keyframes of
+// 320 x 240, us a solve: textbook FP64, automatic shape of 512 x 1, 6884 with one
+// workgroup on a compute unit, 4142 with two; 256 x 6, 2275 with one, 1507 with two;
+// 256 x 2 with Tukey's cost, 5353 with two, 3889 with three). A keyframe alone has
+// at most 256 workgroups, one per compute unit: there a bound only costs (640 x 480
+// textbook, 512 x 4: 1155 against 1020; 512 x 3 with Tukey's cost: 616 against 587),
+// except for the plain 512 x 3 that 640 x 480 takes, where it is free (585 against
+// 583) and leaves half of a unit's registers to others.
+constexpr int solve_waves(int elt, int nt, int ppt, bool pipe, bool var, bool batch) {
+  if (!batch) return elt == 4 && nt == 512 && ppt == 3 && pipe && !var ? 4 : 1;
+  if (elt == 8) {
+    if (pipe) return 1;
+    if (nt == 512) return ppt == 1 ? 4 : 1;
+    return nt == 256 && ppt == 2 ? 3 : (nt == 256 && ppt == 6 ? 2 : 1);
+  }
+  if (nt == 512) return ppt <= 4 ? 4 : 1;
+  return nt == 256 && ppt == 4 && pipe ? 3 : 1;
+}
+
 template <typename T, int NT, int PPT, bool PIPE, bool VAR>
-__global__ __launch_bounds__(NT) void k_solve(SolveArgs a) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(solve_waves(sizeof(T), NT, PPT, PIPE, VAR, false))))
+void k_solve(SolveArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   solve_member<T, NT, PPT, PIPE, VAR>(a, blockIdx.x, smem);
 }
@@ -1036,12 +1058,11 @@ __global__ __launch_bounds__(NT) void k_solve(SolveArgs a) {
 // Batched form: workgroup g works through its queue of (keyframe, member)
 // entries in order. Queues list teams in one global order, so the lowest
 // unfinished team always has every member at it and the launch cannot
-// deadlock, provided all workgroups are co-resident. FP32 512-thread
-// workgroups of up to 4 pixels per thread are held to 128 registers so that two
-// of them share a compute unit (one computes while the other's team
-// synchronises).
+// deadlock, provided all workgroups are co-resident. Several workgroups share a
+// compute unit where their registers allow (solve_waves): one computes while the
+// other's team synchronises.
 template <typename T, int NT, int PPT, bool PIPE, bool VAR>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && NT == 512 && NT * PPT <= 2048 ? 4 : 1)))
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(solve_waves(sizeof(T), NT, PPT, PIPE, VAR, true))))
 void k_solve_batch(const SolveArgs* __restrict__ tab,
                                                     const int32_t* __restrict__ queue,
                                                     const int32_t* __restrict__ qoff) {

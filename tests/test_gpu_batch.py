@@ -142,3 +142,28 @@ def test_batch_schedule_fills_the_workgroups():
     batch.close()
     for m in members:
         m.close()
+
+
+@pytest.mark.parametrize("kw,tiles,per_cu", [
+    (dict(precision="f64", solver_threads=512, cg_variant="textbook"), (16, 16), 2),
+    (dict(precision="f64", solver_threads=512, cg_variant="textbook", robust="tukey"), (16, 16), 2),
+    (dict(precision="f64", solver_threads=256, cg_variant="textbook", robust="tukey"), (16, 12), 3),
+    (dict(precision="f64", solver_threads=256, cg_variant="textbook"), (8, 8), 2),
+    (dict(precision="f64", solver_threads=256, cg_variant="textbook", robust="tukey"), (8, 8), 2),
+    (dict(precision="f32", solver_threads=256, cg_variant="pipelined"), (10, 8), 3),
+    (dict(precision="f32", solver_threads=512, cg_variant="pipelined"), (7, 6), 2),
+])
+def test_batch_workgroups_share_a_compute_unit(kw, tiles, per_cu):
+    """The instances whose registers are held to a step, at 1, 2, 4 and 6 pixels per
+    thread: as many workgroups as that step lets a compute unit hold."""
+    from paper_2207_12244_amd.kf import Batch, Keyframe
+    t = torch()
+    n = 3 * 256 * per_cu // (2 * tiles[0] * tiles[1]) + 1
+    members = [Keyframe(320, 240, tiles=tiles, **kw) for _ in range(n)]
+    batch = Batch(members, use_graph=False)
+    lay = batch.layout()
+    say(f"batch residency {kw} tiles {tiles}: {lay}")
+    assert lay["workgroups"] == per_cu * t.cuda.get_device_properties(0).multi_processor_count, lay
+    batch.close()
+    for m in members:
+        m.close()
