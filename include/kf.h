@@ -169,7 +169,10 @@ typedef struct {
    fx = fy = 0.8 width, cx = width / 2, cy = height / 2. */
 void kf_config_default(kf_config* cfg, int32_t width, int32_t height);
 
-/* Device bytes a context with this configuration needs; 0 if cfg is invalid. */
+/* Device bytes a context with this configuration needs on the current device; 0
+   if cfg is invalid. To be asked, not kept: the size follows the solver that the
+   configuration takes (the automatic float form's s-step PCG has a wider boundary
+   exchange than the explicit variants) and may differ between versions. */
 size_t kf_workspace_bytes(const kf_config* cfg);
 
 /* Validates cfg and binds the workspace. No device work. *out = NULL on error.

@@ -223,20 +223,25 @@ bool sstep_applies(const kf_config& c) {
 
 }  // namespace
 
-bool choose_tiling(const kf_config& c, Tiling* t) {
-  const int W = c.width, H = c.height;
+// (An s-step workgroup takes a compute unit, so a team has at most `cus` of them.
+// kf_solve.hip's may share one: on a device with fewer units than the team has
+// workgroups that solver still may have room for it.)
+bool choose_tiling(const kf_config& c, int cus, Tiling* t) {
+  const int W = c.width, H = c.height, most = std::min(MAX_TEAM, cus);
   if (!choose_tiling_classic(W, H, c.solver_tiles_x, c.solver_tiles_y, c.solver_threads, c.precision, t)) return false;
   if (!sstep_applies(c)) return true;
   const int base = t->threads;
   if (c.solver_tiles_x > 0) {
     Tiling f{};
-    if (sstep_grid(W, H, c.solver_tiles_x, c.solver_tiles_y, c.n_cg, &f)) *t = f;
+    if (c.solver_tiles_x * c.solver_tiles_y <= most &&
+        sstep_grid(W, H, c.solver_tiles_x, c.solver_tiles_y, c.n_cg, &f))
+      *t = f;
     t->base_threads = base;
     return true;
   }
   double best = 1e300;
   for (int tx = 1; tx <= 64 && tx <= W; ++tx)
-    for (int ty = 1; ty <= 64 && ty <= H && tx * ty <= MAX_TEAM; ++ty) {
+    for (int ty = 1; ty <= 64 && ty <= H && tx * ty <= most; ++ty) {
       Tiling f{};
       if (!sstep_grid(W, H, tx, ty, c.n_cg, &f)) continue;
       const double cost = sstep_gn_us(f, c.n_cg);
@@ -588,10 +593,19 @@ void kf_config_default(kf_config* cfg, int32_t width, int32_t height) {
   cfg->precision = KF_F32;
 }
 
+static int current_cus() {   // of the current device; 256 without one
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) {
+    (void)hipGetLastError();
+    device = 0;
+  }
+  return device_cus(device);
+}
+
 size_t kf_workspace_bytes(const kf_config* cfg) {
   if (!cfg || validate(*cfg)) return 0;
   Tiling t;
-  if (!choose_tiling(*cfg, &t)) return 0;
+  if (!choose_tiling(*cfg, current_cus(), &t)) return 0;
   Layout L;
   layout_for(*cfg, t, &L);
   return L.total;
@@ -603,7 +617,7 @@ kf_status kf_create(const kf_config* cfg, kf_ctx** out) {
   if (!cfg) return KF_ERR_ARG;
   if (validate(*cfg)) return KF_ERR_ARG;
   Tiling t;
-  if (!choose_tiling(*cfg, &t)) return KF_ERR_ARG;
+  if (!choose_tiling(*cfg, current_cus(), &t)) return KF_ERR_ARG;
   Layout L;
   layout_for(*cfg, t, &L);
   if (!cfg->workspace) return KF_ERR_ARG;

@@ -120,8 +120,9 @@ constexpr int MAX_TEAM = 256;        // workgroups per keyframe team
 constexpr int CHUNK = 256;           // pixels per compaction chunk
 #define KF_BATCH_MAX KF_BATCH_MAX_MEMBERS
 
-// The decomposition of a configuration: the s-step solver's where it applies.
-bool choose_tiling(const kf_config& c, Tiling* t);
+// The decomposition of a configuration on a device of `cus` compute units: the
+// s-step solver's where it applies.
+bool choose_tiling(const kf_config& c, int cus, Tiling* t);
 // kf_solve.hip's alone.
 bool choose_tiling_classic(int W, int H, int tx_req, int ty_req, int threads_req, int prec, Tiling* t);
 double iteration_us(const Tiling& t);   // latency model of one PCG iteration (kf_solve.hip)

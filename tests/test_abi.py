@@ -172,3 +172,37 @@ def test_batch_rejects_incompatible_members_on_the_host():
     finally:
         for h in (a, b, c, d, e):
             kf.kf_destroy(h)
+
+
+class _Tiling(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("tiles_x", "tiles_y", "tile_w", "tile_h", "blocks", "ppt", "threads", "s",
+                                            "rows", "cells", "base_threads")]
+
+
+def _tiling(kf, lib, cus, W, H, **fields):
+    cfg = kf.kf_config_default(W, H)
+    for k, v in fields.items():
+        setattr(cfg, k, v)
+    f = lib["_ZN2kf13choose_tilingERK9kf_configiPNS_6TilingE"]
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
+    t = _Tiling()
+    return t if f(ctypes.byref(cfg), cus, ctypes.byref(t)) else None
+
+
+@pytest.mark.parametrize("cus", [256, 128, 64, 32])
+@pytest.mark.parametrize("size", [(64, 48), (160, 120), (333, 251), (640, 480), (1280, 960)])
+def test_sstep_team_fits_the_compute_units(size, cus):
+    """A workgroup of the s-step solver takes a compute unit: a device with fewer of
+    them gets a smaller team of it, or the solver whose workgroups share one, with
+    the tiling that it always had. An explicit tile grid is kept either way."""
+    kf, lib = _lib()
+    t = _tiling(kf, lib, cus, *size)
+    classic = _tiling(kf, lib, cus, *size, cg_variant=2)
+    assert classic.s == 0
+    if t.s:
+        assert t.blocks <= cus
+    else:
+        assert (t.tiles_x, t.tiles_y, t.threads, t.ppt) == (classic.tiles_x, classic.tiles_y, classic.threads, classic.ppt)
+    e = _tiling(kf, lib, cus, *size, solver_tiles_x=16, solver_tiles_y=12)
+    if e is not None:
+        assert (e.tiles_x, e.tiles_y) == (16, 12) and (e.s == 0 or 192 <= cus)
