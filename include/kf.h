@@ -109,7 +109,7 @@ typedef struct {
   double cg_rtol;               /* > 0: PCG until ||r|| <= cg_rtol ||b||, at most cg_max */
   int32_t cg_max;               /* cap of the tolerance mode, >= 1 */
   int32_t cg_variant;           /* 0 automatic: with cg_rtol == 0 pipelined, and in the float
-                                   precisions with solver_threads 0 s-step PCG; 1 textbook PCG;
+                                   precisions with solver_threads 0 and n_cg >= 3 s-step PCG; 1 textbook PCG;
                                    2 pipelined PCG. Same iterates in exact arithmetic; one team
                                    synchronisation per iteration (pipelined) or per 2 or 4 (s-step)
                                    instead of two */

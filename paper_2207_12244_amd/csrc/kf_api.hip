@@ -215,10 +215,15 @@ bool sstep_grid(int W, int H, int tx, int ty, int n_cg, Tiling* t) {
 // Configurations whose depth steps the s-step solver makes: the automatic CG
 // variant with a fixed count in the float precisions, with pairwise terms. An
 // explicit workgroup size asks for kf_solve.hip, whose kernels have that choice
-// (and whose results, to the last bit, such a configuration has always had).
+// (and whose results, to the last bit, such a configuration has always had). So do
+// one or two iterations: the block that makes them is one synchronisation, like
+// theirs, and the longer strips take longer to assemble (10 x 1 iterations, us a
+// solve, pipelined against s-step: 64 x 48 67, 96; 320 x 240 71, 112; 640 x 480
+// 102, 119; 1024 x 768 137, 210. 10 x 2: 89, 95; 93, 111; 126, 118; 166, 208.
+// 10 x 3: 110, 72; 114, 99; 151, 153; 191, 257).
 bool sstep_applies(const kf_config& c) {
   return c.precision != KF_F64 && c.cg_rtol == 0.0 && c.cg_variant == 0 && c.variant != KF_VARIANT_NO_PAIRWISE &&
-         c.solver_threads == 0 && solve_epoch_bound(c) < 30000;
+         c.n_cg >= 3 && c.solver_threads == 0 && solve_epoch_bound(c) < 30000;
 }
 
 }  // namespace

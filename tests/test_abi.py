@@ -206,3 +206,12 @@ def test_sstep_team_fits_the_compute_units(size, cus):
     e = _tiling(kf, lib, cus, *size, solver_tiles_x=16, solver_tiles_y=12)
     if e is not None:
         assert (e.tiles_x, e.tiles_y) == (16, 12) and (e.s == 0 or 192 <= cus)
+
+
+@pytest.mark.parametrize("size", [(64, 48), (320, 240), (1024, 768)])
+def test_one_or_two_iterations_take_the_pipelined_solver(size):
+    kf, lib = _lib()
+    for n_cg in (1, 2, 3, 20):
+        t, p = _tiling(kf, lib, 256, *size, n_cg=n_cg), _tiling(kf, lib, 256, *size, n_cg=n_cg, cg_variant=2)
+        assert p.s == 0
+        assert bytes(t) == bytes(p) if n_cg < 3 else t.s > 0
