@@ -128,7 +128,8 @@ __device__ inline double quad_bcast(double v) {   // lane K's value of each quad
 // W = L D L^T and a = W^-1 (m_0 .. m_q-1) on the first q < S directions, or on
 // those before a pivot that vanishes: the block's directions are dependent, CG
 // has converged and ends with this block (returns false). The slow way, for a
-// last block of fewer iterations and for convergence.
+// last block of fewer iterations, for convergence, and for a residual that is not
+// finite.
 template <int S>
 __device__ __forceinline__ bool solve_leading(SsHead<S>* hd, const double* m, int q, double* a) {
   double L[S][S], D[S], iD[S];
@@ -155,6 +156,7 @@ __device__ __forceinline__ bool solve_leading(SsHead<S>* hd, const double* m, in
 #pragma unroll
     for (int k = i + 1; k < S; ++k) a[i] -= L[k][i] * a[k];
     if (i >= q || iD[i] == 0.0) a[i] = 0.0;
+    if (!(m[0] < (double)INFINITY)) a[i] = m[0] - m[0];   // shown, not passed over: x becomes NaN
   }
   return good;
 }
@@ -909,7 +911,7 @@ __device__ __forceinline__ void sstep_member(const SolveArgs& a, const int b, un
         if (DEFER && pending) directions();
       };
       auto use = [&](const double* t) {
-        const bool some = t[0] > 0.0;
+        const bool some = t[0] != 0.0;
         bool good = false;
         if (some) good = bs.finish(hd, hd->coef[cbuf ^ 1], t, first, q, lane);
         if (lane == 0) hd->stop = some ? (good ? 0 : 1) : 2;

@@ -474,3 +474,28 @@ def test_solver_one_tile_shapes(W, H):
     kf, err, dtau = _random_state_solve(W, H, (1, 1), 15, threads=512)
     gu.say(f"[solver-one-tile] {W}x{H} max|dx| {err.max():.3e} dtau {dtau:.3e}")
     assert err.max() <= 2e-4 and np.sqrt(np.mean(err ** 2)) <= 2e-5 and dtau <= 2e-5
+
+
+@pytest.mark.parametrize("W,H,tiles", [(16, 16, (1, 1)), (64, 48, (8, 6)), (64, 48, (1, 1)), (160, 120, (2, 2))])
+@pytest.mark.parametrize("x_at", [3e38, -3e38])
+def test_solver_residual_not_finite(W, H, tiles, x_at):
+    """A state whose residual overflows (plain least squares, one log-depth of 3e38)
+    is not passed over: every solver ends with NaN, as division by such a residual
+    gives, not with the state it started from. One and several workgroups, 2 and 4
+    iterations per synchronisation."""
+    from paper_2207_12244_amd.kf import Keyframe
+    t = gu.torch()
+    one = np.ones((H, W))
+    for variant in ("auto", "pipelined"):
+        K = np.array([[0.8 * W, 0.0, W / 2.0], [0.0, 0.8 * W, H / 2.0], [0.0, 0.0, 1.0]])
+        kf = Keyframe(W, H, precision="f32", n_gn=2, n_cg=8, K=K, tiles=tiles, huber_delta=float("inf"), cg_variant=variant)
+        kf.set_prior(gu.dev(0 * one, t.uint8),
+                     *[gu.dev(m, t.float32) for m in (0 * one, 1e-2 * one, 0 * one, 1e-2 * one, 0 * one, 1e-2 * one)], np.eye(4))
+        x = 0 * one
+        x[H // 2, W // 3] = x_at
+        kf.import_state(x=gu.dev(x, t.float32))
+        kf.solve()
+        st = kf.export_state()
+        gu.say(f"[solver-overflow] {W}x{H} tiles {tiles} {variant}: {int(t.isnan(st['x']).sum())} of {W * H} NaN")
+        assert bool(t.isnan(st["x"]).all())
+        kf.close()
