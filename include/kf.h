@@ -270,12 +270,14 @@ kf_status kf_fuse_frame_static(kf_ctx* ctx, const uint8_t* image1, const double 
 kf_status kf_read_stats(kf_ctx* ctx, kf_frame_stats* out);
 
 /* Measurement aid, not part of the method: enqueues on cfg.stream one launch
-   of the solver's workgroup team (same tiling, workgroup size and exchange
-   words as kf_solve) that makes `rounds` team synchronisations of the kind one
-   pipelined PCG iteration makes (`nvalues` inner-product partials, 1..3, plus
-   the tile boundary of the stencil operand) and no arithmetic. The caller times
-   it (events on cfg.stream); time / rounds is the synchronisation latency that
-   bounds the solve. rounds in [1, 20000]. KF_ERR_STATE before kf_set_prior or
+   of the solver's workgroup team (same tile grid and workgroup size as kf_solve;
+   the exchange is that of pipelined PCG, also where kf_solve takes s-step PCG,
+   whose synchronisations carry 4 or 8 partials and wider boundaries) that makes
+   `rounds` team synchronisations of the kind one pipelined PCG iteration makes
+   (`nvalues` inner-product partials, 1..3, plus the tile boundary of the stencil
+   operand) and no arithmetic, behind a clear of the exchange words. The caller
+   times it (events on cfg.stream); time / rounds is the latency of such a
+   synchronisation. rounds in [1, 20000]. KF_ERR_STATE before kf_set_prior or
    with pipeline_frames; the resident depth state is not touched. */
 kf_status kf_probe_sync(kf_ctx* ctx, int32_t rounds, int32_t nvalues);
 

@@ -959,7 +959,10 @@ kf_status kf_probe_sync(kf_ctx* c, int32_t rounds, int32_t nvalues) {
   if (nvalues < 1 || nvalues > NV_MAX) return fail(c, KF_ERR_ARG, "kf_probe_sync: nvalues must be in [1, 3]");
   const uint32_t bound = (uint32_t)rounds + 2;
   hipError_t e = epoch_wrap_if_needed(c, bound);
-  if (e != hipSuccess) return hip_fail(c, e, "kf_probe_sync (epoch wrap)");
+  // it waits for tagged words where s-step PCG leaves pixel data, which a new
+  // keyframe does not clear, and where its own of any earlier call still are
+  if (e == hipSuccess) e = launch_zero(c->ws + c->lay.parts, c->lay.total - c->lay.parts, c->stream);
+  if (e != hipSuccess) return hip_fail(c, e, "kf_probe_sync (clear)");
   SolveArgs a;
   solve_args(c, &a);
   a.epoch_span = bound;

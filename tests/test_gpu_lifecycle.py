@@ -178,3 +178,29 @@ def test_contexts_on_different_streams(pipelined):
         for k in ("x", "rho", "var", "match"):
             assert np.array_equal(a[k], b[k]), (i, k)
         assert a["tau"] == b["tau"], i
+
+
+@pytest.mark.parametrize("cg_variant", ["auto", "pipelined"])
+def test_probe_starts_from_cleared_words(cg_variant):
+    """The synchronisation probe waits for tagged words; none may be left from a
+    solve, an earlier probe or another use of the workspace (here: a pattern),
+    also where a new keyframe does not clear them."""
+    from paper_2207_12244_amd.kf import Keyframe
+    t = gu.torch()
+    W, H = 160, 120
+    K = np.array([[0.8 * W, 0.0, W / 2.0], [0.0, 0.8 * W, H / 2.0], [0.0, 0.0, 1.0]])
+    kf = Keyframe(W, H, precision="f32", K=K, cg_variant=cg_variant)
+    kf.workspace.fill_(0xA5)
+    z = t.zeros((H, W), dtype=t.float32, device="cuda")
+    img = t.zeros((H, W), dtype=t.uint8, device="cuda")
+    for _ in range(2):
+        kf.set_prior(img, z, z + 1, z, z + 1, z, z + 1, np.eye(4))
+        kf.probe_sync(1, 1)
+        t.cuda.synchronize()
+        lay = kf.solver_layout()
+        words = 2 * lay["tiles_x"] * lay["tiles_y"] * 2 * 2 * (lay["tile_w"] + lay["tile_h"]) * 2   # kf_solve.hip's boundary
+        end = -kf.workspace.data_ptr() % 256 + kf.cfg.workspace_bytes
+        tail = kf.workspace[end - 8 * words:end].view(t.int64).cpu().numpy()
+        assert not (tail == np.frombuffer(b"\xa5" * 8, np.int64)[0]).any()
+        assert kf.stats().team_syncs == 1
+    kf.close()
