@@ -254,13 +254,13 @@ kf_status kf_read_depth(kf_ctx* ctx, void* depth_out, void* var_out, double* sca
 /* For callers that cannot allocate device memory (code under HIP graph
    capture, serving loops and harnesses that forbid allocation): kf_fuse_frame
    with the same results, whose kernels take their scratch -- the staged new
-   frame and the solver team's exchange words -- from a fixed array inside the
-   library (24 MiB per device, held until the process ends) instead of the
+   frame and the solver team's tagged exchange words -- from a fixed array inside
+   the library (4.2 MiB per device, held until the process ends) instead of the
    context's workspace. Allocates nothing and calls no allocating routine.
    KF_ERR_ARG if the keyframe needs more than 4 MiB of scratch, counted with the
    exchange words of pipelined PCG ((height + 1) x row stride of the staged
    frame, rows padded to a multiple of 64 bytes >= width + 8, plus those words:
-   640 x 480 needs 2.8 MB); the array holds what s-step PCG takes beyond that;
+   640 x 480 needs 2.8 MB; the pixel data of s-step PCG stays in the workspace);
    KF_ERR_STATE before kf_set_prior or with pipeline_frames. Every call on a
    device shares that device's array and clears what must start at zero, so
    calls that overlap on one device (contexts on different streams) race. */

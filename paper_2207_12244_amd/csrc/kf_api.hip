@@ -519,19 +519,23 @@ namespace {
 // holds its own copy for the life of the process; host code uses only the
 // per-device address that hipGetSymbolAddress returns, never the symbol.
 // Which keyframes it takes is decided on the staged frame and kf_solve.hip's
-// exchange words (static_need, at most KF_STATIC_LIMIT_BYTES). The s-step
-// solver's words of every such keyframe fit the array: at most 256 tiles with
-// tile_w + tile_h <= 248 (sstep_fit) take 2 * 4 * 256 * 10 * 248 * 4 bytes of pixel
-// data (19.4 MiB) and 0.2 MiB of lines, beside at most 4 MiB of staged frame.
+// exchange words (static_need, at most KF_STATIC_LIMIT_BYTES). Of the s-step
+// solver's, the lines are here (they carry tags, so every call clears them; beside
+// the staged frame of any such keyframe there is room for those of the largest
+// team), while its pixel data, which needs no clear and is several times as much,
+// stays in the context's workspace.
 constexpr size_t KF_STATIC_LIMIT_BYTES = (size_t)4 << 20;
-constexpr size_t KF_STATIC_SCRATCH_BYTES = (size_t)24 << 20;
+constexpr size_t KF_STATIC_SCRATCH_BYTES = KF_STATIC_LIMIT_BYTES + (size_t)2 * NV_MAX * PART_REPLICAS * MAX_TEAM * 2 * 8;
 static __device__ __align__(256) unsigned char scratch[KF_STATIC_SCRATCH_BYTES];
 
-size_t static_need(const kf_config& g) {
+size_t static_need(kf_ctx* c) {
+  if (c->static_need) return c->static_need;   // of the configuration, so it is searched for once
+  const kf_config& g = c->cfg;
   Tiling t{};
-  if (!choose_tiling_classic(g.width, g.height, g.solver_tiles_x, g.solver_tiles_y, g.solver_threads, g.precision, &t))
-    return SIZE_MAX;
-  return align256((size_t)(g.height + 1) * stage_stride(g.width)) + partial_words_bytes(t) + exchange_words_bytes(t);
+  c->static_need = SIZE_MAX;
+  if (choose_tiling_classic(g.width, g.height, g.solver_tiles_x, g.solver_tiles_y, g.solver_threads, g.precision, &t))
+    c->static_need = align256((size_t)(g.height + 1) * stage_stride(g.width)) + partial_words_bytes(t) + exchange_words_bytes(t);
+  return c->static_need;
 }
 
 constexpr int KF_MAX_DEVICES = 64;
@@ -914,11 +918,12 @@ kf_status kf_fuse_frame_static(kf_ctx* c, const uint8_t* image1, const double T_
   if (!image1) return fail(c, KF_ERR_ARG, "kf_fuse_frame_static: NULL image");
   if (!pose_ok(T_wc1)) return fail(c, KF_ERR_ARG, "kf_fuse_frame_static: pose must be finite with last row 0 0 0 1");
   const size_t stage = align256((size_t)(c->cfg.height + 1) * stage_stride(c->cfg.width));
-  const size_t exch = c->lay.total - c->lay.parts;   // exchange words of the solver team
-  const size_t need = static_need(c->cfg);
+  const bool sstep = c->tiling.s != 0;
+  const size_t exch = (sstep ? c->lay.halo : c->lay.total) - c->lay.parts;   // the team's words in the array
+  const size_t need = static_need(c);
   if (need > KF_STATIC_LIMIT_BYTES || stage + exch > KF_STATIC_SCRATCH_BYTES)
     return fail(c, KF_ERR_ARG, "kf_fuse_frame_static: this keyframe needs " + std::to_string(need) +
-                                   " bytes of scratch, the static array holds " +
+                                   " bytes of scratch, the static array is for keyframes of at most " +
                                    std::to_string(KF_STATIC_LIMIT_BYTES));
   char* base = nullptr;
   hipError_t e = static_scratch(c->device, &base);
@@ -938,7 +943,7 @@ kf_status kf_fuse_frame_static(kf_ctx* c, const uint8_t* image1, const double T_
   SolveArgs sa;
   solve_args(c, &sa);
   sa.parts = reinterpret_cast<uint64_t*>(base + stage);
-  sa.halo = reinterpret_cast<uint64_t*>(base + stage + (c->lay.halo - c->lay.parts));
+  if (!sstep) sa.halo = reinterpret_cast<uint64_t*>(base + stage + (c->lay.halo - c->lay.parts));
   const int kind = solve_kind(g);
   if (c->coresident < 0) c->coresident = solve_max_coresident(g.precision, c->tiling, kind, c->device);
   if (c->coresident < c->tiling.blocks)

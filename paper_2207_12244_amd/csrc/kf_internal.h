@@ -307,6 +307,7 @@ struct kf_ctx {
   bool solve_pending[2] = {false, false};
   int last_solve = -1;                    // buffer of the last enqueued solve
   bool solves_waited = true;              // the user stream waits for every enqueued solve
+  size_t static_need = 0;                 // scratch that kf_fuse_frame_static counts (0: not counted yet)
   void* lane = nullptr;                   // of the solves' stream (kf_admit.h), from the first solve on
 };
 

@@ -215,3 +215,16 @@ def test_one_or_two_iterations_take_the_pipelined_solver(size):
         t, p = _tiling(kf, lib, 256, *size, n_cg=n_cg), _tiling(kf, lib, 256, *size, n_cg=n_cg, cg_variant=2)
         assert p.s == 0
         assert bytes(t) == bytes(p) if n_cg < 3 else t.s > 0
+
+
+def test_static_array_holds_its_limit_and_little_more():
+    """kf_fuse_frame_static's array, which every process that loads the library
+    has on each device: 4 MiB and the lines of the largest team."""
+    import shutil
+    import subprocess
+    kf, lib = _lib()
+    if not shutil.which("nm"):
+        pytest.skip("no nm")
+    out = subprocess.run(["nm", "-S", kf.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    sizes = [int(l.split()[1], 16) for l in out.splitlines() if re.search(r"\b[bB] .*7scratchE", l)]
+    assert len(sizes) == 1 and (4 << 20) <= sizes[0] <= (4 << 20) + (256 << 10)

@@ -61,3 +61,40 @@ def test_fuse_frame_static_rejects_oversized_keyframes():
     assert st == K.KF_ERR_ARG and b"static array" in lib.kf_last_error(kf.ctx)
     kf.read_depth()
     kf.close()
+
+
+@pytest.mark.parametrize("cg_variant", ["auto", "pipelined"])
+def test_fuse_frame_static_at_its_limit(cg_variant):
+    """The largest team (16 x 16 tiles of 1024 x 400), whose exchange words take most
+    of the array, called in turn with kf_fuse_frame, which uses the workspace's."""
+    from paper_2207_12244_amd import kf as K
+    from paper_2207_12244_amd.kf import Keyframe
+    t = gu.torch()
+    lib = K.load_library()
+    W, H = 1024, 400
+    rng = np.random.default_rng(5)
+    img = rng.integers(0, 256, (H, W)).astype(np.uint8)
+    Kc = np.array([[0.8 * W, 0.0, W / 2.0], [0.0, 0.8 * W, H / 2.0], [0.0, 0.0, 1.0]])
+    z = t.zeros((H, W), dtype=t.float32, device="cuda")
+    pose = np.eye(4)
+    pose[0, 3] = 0.05
+    kfs = []
+    for _ in range(2):
+        kf = Keyframe(W, H, precision="f32", n_samples=8, n_gn=3, K=Kc, tiles=(16, 16), cg_variant=cg_variant)
+        kf.set_prior(gu.dev(img, t.uint8), z, z + 1, z, z + 1, z, z + 1, np.eye(4))
+        kfs.append(kf)
+    ref, sta = kfs
+    d = gu.dev(np.roll(img, 9, 1), t.uint8)
+    for call in ("static", "own", "static"):
+        ref.fuse_frame(d, pose)
+        if call == "own":
+            sta.fuse_frame(d, pose)
+        else:
+            assert lib.kf_fuse_frame_static(sta.ctx, ctypes.c_void_p(d.data_ptr()), K._pose(pose)) == K.KF_OK
+    a, b = gu.np_state(ref), gu.np_state(sta)
+    for k in ("x", "rho", "var", "match"):
+        assert np.array_equal(a[k], b[k]), k
+    assert a["tau"] == b["tau"]
+    for kf in kfs:
+        kf.close()
+
