@@ -68,13 +68,17 @@ Device* admission_of(int device) {
 
 }  // namespace
 
-hipError_t admit_launch(kf_ctx* c, hipStream_t s, int blocks, int coresident, hipError_t (*go)(void*), void* arg) {
+bool admit_join(kf_ctx* c) {
+  if (c->lane) return true;
   Device* d = admission_of(c->device);
-  if (d && !c->lane) c->lane = d->join(s);
-  if (!c->lane) return hipErrorOutOfMemory;
-  const int per_cu = coresident / c->cus;
-  return d->launch(static_cast<Device::Lane*>(c->lane), blocks, per_cu, hipSuccess, hipErrorInvalidHandle,
-                   [&] { return go(arg); });
+  c->lane = d ? d->join(c->solve_stream ? c->solve_stream : c->stream) : nullptr;
+  return c->lane != nullptr;
+}
+
+hipError_t admit_launch(kf_ctx* c, int blocks, int coresident, hipError_t (*go)(void*), void* arg) {
+  return admission_of(c->device)
+      ->launch(static_cast<Device::Lane*>(c->lane), blocks, coresident / c->cus, hipSuccess, hipErrorInvalidHandle,
+               [&] { return go(arg); });
 }
 
 void admit_leave(kf_ctx* c) {

@@ -705,6 +705,7 @@ namespace {
 // from the six caller maps.
 kf_status set_prior_impl(kf_ctx* c, const uint8_t* image0, const void* const maps[6], const double* T_wc0,
                          const ResampleArgs* rs) {
+  if (!admit_join(c)) return fail(c, KF_ERR_HIP, "kf_set_prior: no event for the solves' stream");
   std::memcpy(c->T_wc0, T_wc0, sizeof(c->T_wc0));
   // exchange words and device scalars start from zero (epoch 0 is never used)
   hipError_t e = wait_solves(c);
@@ -845,7 +846,7 @@ kf_status kf_solve(kf_ctx* c) {
     if (e == hipSuccess) e = hipStreamWaitEvent(s, c->ev_user, 0);
     if (e != hipSuccess) return hip_fail(c, e, "kf_solve (ordering)");
   }
-  e = admitted(c, s, c->tiling.blocks, c->coresident,
+  e = admitted(c, c->tiling.blocks, c->coresident,
                [&] { return launch_solve(g.precision, c->tiling, a, g.solver_cooperative != 0, kind, s); });
   if (e == hipSuccess && g.pipeline_frames) {
     e = hipEventRecord(c->ev_solve[c->cur], s);
@@ -949,7 +950,7 @@ kf_status kf_fuse_frame_static(kf_ctx* c, const uint8_t* image1, const double T_
   if (c->coresident < c->tiling.blocks)
     return fail(c, KF_ERR_ARG, "solver tiling needs " + std::to_string(c->tiling.blocks) +
                                " co-resident workgroups, the device holds " + std::to_string(c->coresident));
-  e = admitted(c, c->stream, c->tiling.blocks, c->coresident,
+  e = admitted(c, c->tiling.blocks, c->coresident,
                [&] { return launch_solve(g.precision, c->tiling, sa, g.solver_cooperative != 0, kind, c->stream); });
   if (e != hipSuccess) return hip_fail(c, e, "kf_fuse_frame_static (solve)");
   c->epoch += bound;
@@ -974,7 +975,7 @@ kf_status kf_probe_sync(kf_ctx* c, int32_t rounds, int32_t nvalues) {
   a.packed = (c->cfg.precision != KF_F64 && bound < 30000) ? 1 : 0;
   if (c->coresident < 0) c->coresident = solve_max_coresident(c->cfg.precision, c->tiling, solve_kind(c->cfg), c->device);
   if (c->coresident < c->tiling.blocks) return fail(c, KF_ERR_ARG, "kf_probe_sync: tiling not co-resident");
-  e = admitted(c, c->stream, c->tiling.blocks, c->coresident,
+  e = admitted(c, c->tiling.blocks, c->coresident,
                [&] { return launch_sync_probe(c->cfg.precision, c->tiling, a, rounds, nvalues, c->stream); });
   if (e != hipSuccess) return hip_fail(c, e, "kf_probe_sync");
   c->epoch += bound;

@@ -268,7 +268,7 @@ kf_status run_call(kf_batch* b, int which, const std::vector<int>& active, const
       blocks = std::max(blocks, fam.grid);
       coresident = coresident ? std::min(coresident, fam.capacity) : fam.capacity;
     }
-    e = admitted(b->m[0], b->stream, blocks, coresident, go);
+    e = admitted(b->m[active[0]], blocks, coresident, go);   // (members share the stream)
   } else if (e == hipSuccess) {
     e = go();
   }

@@ -268,13 +268,17 @@ __host__ __device__ inline int sstep_frame_words(int tile_w, int tile_h, int s) 
 }
 // Compute units of the device (256 if the query fails).
 int device_cus(int device);
-// Launches a solver team of c's by go(arg) on stream s (always the same one of a
-// context), ordered behind the launches of other streams that it could not be
-// resident with. coresident: workgroups of its kernel that the device holds.
-hipError_t admit_launch(kf_ctx* c, hipStream_t s, int blocks, int coresident, hipError_t (*go)(void*), void* arg);
+// Admission of solver launches (kf_admit.h): the stream of c's solves takes part in
+// it from the first keyframe on, so that solves allocate nothing. False: out of
+// memory, or the device gave no event.
+bool admit_join(kf_ctx* c);
+// Launches a solver team by go(arg) on that stream, ordered behind the launches of
+// other streams that it could not be resident with. coresident: workgroups of its
+// kernel that the device holds.
+hipError_t admit_launch(kf_ctx* c, int blocks, int coresident, hipError_t (*go)(void*), void* arg);
 template <typename F>
-hipError_t admitted(kf_ctx* c, hipStream_t s, int blocks, int coresident, const F& go) {
-  return admit_launch(c, s, blocks, coresident, [](void* f) { return (*static_cast<const F*>(f))(); },
+hipError_t admitted(kf_ctx* c, int blocks, int coresident, const F& go) {
+  return admit_launch(c, blocks, coresident, [](void* f) { return (*static_cast<const F*>(f))(); },
                       const_cast<F*>(&go));
 }
 void admit_leave(kf_ctx* c);   // before the stream goes
@@ -308,7 +312,7 @@ struct kf_ctx {
   int last_solve = -1;                    // buffer of the last enqueued solve
   bool solves_waited = true;              // the user stream waits for every enqueued solve
   size_t static_need = 0;                 // scratch that kf_fuse_frame_static counts (0: not counted yet)
-  void* lane = nullptr;                   // of the solves' stream (kf_admit.h), from the first solve on
+  void* lane = nullptr;                   // of the solves' stream (kf_admit.h), from the first keyframe on
 };
 
 namespace kf {
