@@ -944,6 +944,10 @@ kf_status kf_fuse_frame_static(kf_ctx* c, const uint8_t* image1, const double T_
   SolveArgs sa;
   solve_args(c, &sa);
   sa.parts = reinterpret_cast<uint64_t*>(base + stage);
+  // and its epochs can be used again: counted on, those of the workspace's words
+  // would lie any number of calls back at the next kf_solve, whose 16-bit tags
+  // tell epochs apart within one launch's span only
+  sa.epoch_span = 0;
   if (!sstep) sa.halo = reinterpret_cast<uint64_t*>(base + stage + (c->lay.halo - c->lay.parts));
   const int kind = solve_kind(g);
   if (c->coresident < 0) c->coresident = solve_max_coresident(g.precision, c->tiling, kind, c->device);
@@ -953,7 +957,6 @@ kf_status kf_fuse_frame_static(kf_ctx* c, const uint8_t* image1, const double T_
   e = admitted(c, c->tiling.blocks, c->coresident,
                [&] { return launch_solve(g.precision, c->tiling, sa, g.solver_cooperative != 0, kind, c->stream); });
   if (e != hipSuccess) return hip_fail(c, e, "kf_fuse_frame_static (solve)");
-  c->epoch += bound;
   return KF_OK;
 }
 

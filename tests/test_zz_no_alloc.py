@@ -98,3 +98,35 @@ def test_fuse_frame_static_at_its_limit(cg_variant):
     for kf in kfs:
         kf.close()
 
+
+
+def test_fuse_frame_static_between_solves():
+    """kf_solve's exchange words carry 16-bit epoch tags: calls of
+    kf_fuse_frame_static, which do not touch them, must not bring their old
+    content a multiple of 65536 epochs back. Here 3 static calls of 16384 epochs
+    (8190 iterations allowed, none needed) lie between two solves."""
+    from paper_2207_12244_amd import kf as K
+    from paper_2207_12244_amd.kf import Keyframe
+    t = gu.torch()
+    lib = K.load_library()
+    W, H = 64, 48
+    rng = np.random.default_rng(11)
+    has = rng.random((H, W)) < 0.3
+    rho = gu.dev(np.where(has, rng.uniform(0.3, 1.2, (H, W)), 0.0), t.float32)
+    var = gu.dev(np.where(has, rng.uniform(1e-4, 1e-2, (H, W)), 0.0), t.float32)
+    z = t.zeros((H, W), dtype=t.float32, device="cuda")
+    img = t.zeros((H, W), dtype=t.uint8, device="cuda")
+    out = []
+    for static in (0, 3):
+        kf = Keyframe(W, H, precision="f32", n_gn=1, n_cg=8190, tiles=(8, 6), cg_variant="pipelined")
+        kf.set_prior(img, z, z + 0.1, z, z + 0.1, z, z + 0.1, np.eye(4))
+        kf.solve()
+        assert kf.stats().team_syncs == 2
+        for _ in range(static):
+            assert lib.kf_fuse_frame_static(kf.ctx, ctypes.c_void_p(img.data_ptr()), K._pose(np.eye(4))) == K.KF_OK
+        kf.import_state(rho=rho, var=var)
+        kf.solve()
+        out.append(gu.np_state(kf))
+        kf.close()
+    assert (out[0]["x"] != 0.0).any()
+    assert np.array_equal(out[0]["x"], out[1]["x"], equal_nan=True) and out[0]["tau"] == out[1]["tau"]
