@@ -305,9 +305,11 @@ kf_status kf_import_state(kf_ctx* ctx, const void* x, const void* rho, const voi
    A batch fuses one new frame into each of n keyframe contexts (the per-frame
    update of Sec. II-B and II-C, unchanged) with three launches for the whole
    batch: frame staging, stereo over the union of the keyframes' textured
-   pixels, and one persistent solver launch in which every keyframe's team of
-   workgroups runs concurrently with the others. Each keyframe keeps its own
-   tiling, so a member's results are bit-identical to kf_fuse_frame on it. */
+   pixels, and one persistent solver launch in which the keyframes' teams of
+   workgroups run concurrently as far as the device holds them (two such launches,
+   one after the other, if some members take s-step PCG and some do not). Each
+   keyframe keeps its own tiling, so a member's results are bit-identical to
+   kf_fuse_frame on it. */
 
 typedef struct kf_batch kf_batch;
 
@@ -327,8 +329,8 @@ void kf_batch_config_default(kf_batch_config* cfg);
 size_t kf_batch_workspace_bytes(kf_ctx* const* members, int32_t n);
 
 /* Binds n distinct contexts (1 <= n <= KF_BATCH_MAX_MEMBERS). Members must share
-   precision, pattern, n_samples, the solver workgroup size and CG variant, the
-   device and cfg->stream, and run without pipeline_frames; they may differ in
+   precision, pattern, n_samples, the solver workgroup size (automatic: the one that
+   the pipelined form would take) and CG variant, the device and cfg->stream, and run without pipeline_frames; they may differ in
    size, intrinsics, tiling and iteration counts. Schedules the solver teams, uploads the static tables and
    (use_graph) captures the graph; allocates two small pinned host buffers.
    KF_ERR_ARG if the members are incompatible or a team cannot be co-resident.
@@ -354,14 +356,15 @@ kf_status kf_batch_fuse_subset(kf_batch* batch, int32_t n_active, const int32_t*
 
 /* The two halves of kf_batch_fuse, for callers that time or interleave them:
    the stereo update of every member (staging + stereo launches), and the
-   optimisation of every member (the persistent solver launch). Same
+   optimisation of every member (the solver launches). Same
    arguments, conditions and results as the corresponding parts of
    kf_batch_fuse. */
 kf_status kf_batch_stereo_update(kf_batch* batch, const uint8_t* const* images, const double* poses);
 kf_status kf_batch_solve(kf_batch* batch);
 
-/* Solver launch of the batch: workgroups, threads per workgroup, pixels per
-   thread, and the longest per-workgroup team queue. */
+/* Solver launch of the batch: workgroups, threads per workgroup, most pixels per
+   thread, and the longest per-workgroup team queue (of the launch with more
+   workgroups, if there are two). */
 kf_status kf_batch_layout(const kf_batch* batch, int32_t out[4]);
 
 /* Message of the last failure on the batch ("" if none). */

@@ -1,6 +1,6 @@
 // Batched executor: many keyframe contexts, each fused with one new frame, by
-// one staging, one stereo and one persistent solver launch per call. The
-// per-keyframe solver arguments live in a static device table; each call
+// one staging, one stereo and one persistent solver launch (two, where members
+// take both solvers) per call. The per-keyframe solver arguments live in a static device table; each call
 // uploads (from double-buffered pinned host memory, in one copy) the
 // per-frame part: the active member count, their stereo arguments (image
 // pointer and epipolar constants) and the solver's per-workgroup team queues.
@@ -64,7 +64,7 @@ struct kf_batch {
   hipStream_t stream = nullptr;
   hipStream_t capture = nullptr;   // private stream the graphs are captured on
   int device = 0;
-  int prec = 0, pattern = 0, ns = 0, threads = 0, ppt = 0;
+  int prec = 0, pattern = 0, ns = 0;
   Family fam[FAMILIES];
   int cus = 256;   // compute units of the device (stereo grid)
   bool use_graph = true;
@@ -335,7 +335,6 @@ kf_status kf_batch_create(kf_ctx* const* members, int32_t n, const kf_batch_conf
   b->prec = c0->cfg.precision;
   b->pattern = c0->cfg.pattern;
   b->ns = c0->cfg.n_samples;
-  b->threads = c0->tiling.threads;
   b->use_graph = cfg->use_graph != 0;
   b->cus = device_cus(c0->device);
   b->dl = dl;
@@ -355,7 +354,6 @@ kf_status kf_batch_create(kf_ctx* const* members, int32_t n, const kf_batch_conf
     k.sstep = c->tiling.s != 0;
     k.ppt = std::max(k.ppt, c->tiling.ppt);
     k.kind |= solve_kind(c->cfg);
-    b->ppt = std::max(b->ppt, c->tiling.ppt);
     b->fam[f].smem = std::max(b->fam[f].smem, solve_smem_bytes(b->prec, c->tiling));
     blocks[f] += c->tiling.blocks;
     largest[f] = std::max(largest[f], c->tiling.blocks);
@@ -411,13 +409,12 @@ const char* kf_batch_last_error(const kf_batch* b) {
 
 kf_status kf_batch_layout(const kf_batch* b, int32_t out[4]) {
   if (!b || !out) return KF_ERR_ARG;
-  out[0] = out[3] = 0;   // the largest launch, where the members take several kernels
-  out[1] = b->threads;
-  out[2] = b->ppt;
-  for (const Family& f : b->fam) {
-    out[0] = std::max(out[0], f.grid);
-    out[3] = std::max(out[3], f.max_queue);
-  }
+  const Family* f = &b->fam[0];   // the larger launch, where the members take both solvers
+  if (b->fam[1].grid > f->grid) f = &b->fam[1];
+  out[0] = f->grid;
+  out[1] = f->k.threads;
+  out[2] = f->k.ppt;
+  out[3] = f->max_queue;
   return KF_OK;
 }
 

@@ -167,3 +167,102 @@ def test_batch_workgroups_share_a_compute_unit(kw, tiles, per_cu):
     batch.close()
     for m in members:
         m.close()
+
+
+def _auto(case, n_cg=20, tiles=(0, 0), **kw):
+    """A member with the automatic workgroup size: s-step PCG unless kw asks for another."""
+    from paper_2207_12244_amd.kf import Keyframe
+    t = torch()
+    kf = Keyframe(case.W, case.H, K=case.K, n_cg=n_cg, tiles=tiles, precision="f32", n_samples=32, **kw)
+    kf.set_prior(dev(case.image0, t.uint8), *[dev(m, t.float32) for m in case.priors.maps()], case.T_wc0)
+    return kf
+
+
+# one member per strip length of either kernel (a single tile, short and long
+# strips, 2 and 4 iterations per synchronisation), with iteration counts of their own
+AUTO_MEMBERS = [
+    ((64, 48), dict()),
+    ((64, 48), dict(tiles=(1, 1), n_cg=9)),
+    ((160, 120), dict()),
+    ((160, 120), dict(tiles=(2, 2))),
+    ((168, 120), dict(tiles=(2, 2), n_cg=7)),
+    ((320, 240), dict()),
+    ((320, 240), dict(tiles=(6, 4), n_cg=11)),
+    ((320, 240), dict(tiles=(8, 6), n_cg=6)),
+    ((96, 80), dict(tiles=(2, 2))),
+    ((128, 120), dict(tiles=(2, 2), n_cg=5)),
+    ((512, 384), dict()),
+    ((333, 251), dict(n_gn=3)),
+    ((640, 480), dict(n_gn=4)),
+]
+
+
+def _auto_cases(sizes, frames):
+    return [kfsynth.make_case(kfsynth.seed_for(3, 200 + i), W, H, frames, "single") for i, (W, H) in enumerate(sizes)]
+
+
+@pytest.mark.parametrize("mode", ["graph", "direct", "split"])
+@pytest.mark.parametrize("var", [False, True])
+def test_batch_of_sstep_members_equals_solo(mode, var):
+    """Members with the automatic workgroup size, of every strip length, in one
+    launch with more teams than workgroups; var: one of them with Tukey's cost, so
+    that all run the instance that has the variants."""
+    from paper_2207_12244_amd.kf import Batch
+    t = torch()
+    settings = [dict(s) for _, s in AUTO_MEMBERS]
+    if var:
+        settings[2]["robust"] = "tukey"
+    cases = _auto_cases([size for size, _ in AUTO_MEMBERS], 2)
+    solo = [_auto(c, **s) for c, s in zip(cases, settings)]
+    members = [_auto(c, **s) for c, s in zip(cases, settings)]
+    batch = Batch(members, use_graph=mode != "direct")
+    lay = batch.layout()
+    say(f"batch of s-step members, mode {mode} var {var}: {lay}")
+    assert lay["max_queue"] >= 2 and lay["threads"] == 512, lay
+    for f in range(2):
+        imgs = [dev(c.images[f], t.uint8) for c in cases]
+        poses = [c.poses[f] for c in cases]
+        for k, im, p in zip(solo, imgs, poses):
+            k.fuse_frame(im, p)
+        if mode == "split":
+            batch.stereo_update(imgs, poses)
+            batch.solve()
+        else:
+            batch.fuse(imgs, poses)
+        t.cuda.synchronize()
+    for i, (a, b) in enumerate(zip(solo, members)):
+        assert a.stats().team_syncs == b.stats().team_syncs
+        _assert_same(_state(a), _state(b), f"member {i} {AUTO_MEMBERS[i]}")
+        assert np.isfinite(_state(a)["x"]).all()
+    batch.close()
+
+
+def test_batch_of_both_solvers_equals_solo():
+    """Members of both solvers in one batch (two solver launches): all of them, and
+    subsets that leave one or the other without a member."""
+    from paper_2207_12244_amd.kf import Batch
+    t = torch()
+    sizes = [(160, 120), (160, 120), (320, 240), (320, 240), (64, 48)]
+    settings = [dict(), dict(cg_variant="pipelined"), dict(), dict(cg_variant="pipelined"), dict(n_cg=2)]
+    cases = _auto_cases(sizes, 5)
+    solo = [_auto(c, **s) for c, s in zip(cases, settings)]
+    members = [_auto(c, **s) for c, s in zip(cases, settings)]
+    threads = {m.solver_layout()["threads"] for m in members}
+    batch = Batch(members)
+    say(f"batch of both solvers: {batch.layout()}, workgroup sizes {threads}")
+    plan = [[0, 1, 2, 3, 4], [0, 2], [4, 1, 3], [3, 2], [0, 1, 2, 3, 4]]
+    for f, active in enumerate(plan):
+        imgs = [dev(cases[i].images[f], t.uint8) for i in active]
+        poses = [cases[i].poses[f] for i in active]
+        for k, i in enumerate(active):
+            solo[i].fuse_frame(imgs[k], poses[k])
+        if f == 4:
+            batch.stereo_update(imgs, poses)
+            batch.solve()
+        else:
+            batch.fuse_subset(active, imgs, poses)
+        t.cuda.synchronize()
+    for i in range(len(cases)):
+        assert solo[i].stats().team_syncs == members[i].stats().team_syncs
+        _assert_same(_state(solo[i]), _state(members[i]), f"member {i} {sizes[i]} {settings[i]}")
+    batch.close()
