@@ -59,6 +59,24 @@ def solver_bytes_per_frame(N, n_gn, n_cg, word=4):
     return n_gn * (23 + 9 * n_cg) * word * N
 
 
+def solver_io_bytes(N, word=4):
+    """Bytes of one solve's inputs read once and outputs written once: x, the six
+    prior maps, rho and its variance; x."""
+    return 10 * word * N
+
+
+def solver_in_use(cg_variant, n_gn, n_cg, team_syncs):
+    """(CG form, kernel) of a float solve with a fixed count. The automatic form is
+    s-step PCG where it applies, which shows in the synchronisations of a solve:
+    pipelined PCG makes n_cg and one more per Gauss-Newton iteration, s-step PCG
+    at most one for two iterations and one more."""
+    if cg_variant == "textbook":
+        return "textbook", "k_solve"
+    if cg_variant == "auto" and team_syncs <= n_gn * ((n_cg + 1) // 2 + 1) and n_cg > 2:
+        return "s-step", "k_sstep"
+    return "pipelined", "k_solve"
+
+
 def source_hash(*paths):
     """sha256 (16 hex) of source files' code with comments and blank space
     removed, so that comment edits do not invalidate counters of an unchanged kernel."""
@@ -328,17 +346,22 @@ def run_plain_batched(a, torch, cases, wl, imgs, poses, batched_value):
                     "latency-optimal tiling; same frames, poses and settings as the batched form"}
 
 
-def roofline_entry(kernel, bpl, launch_s, traffic, sync=None):
-    """The solver's roofline figures: algorithmic sweep bytes per launch / launch
-    time against HBM peak (achieved, frac), the HBM bytes rocprofv3 counted per
-    launch (traffic) and the rate they give, and the team-synchronisation floor.
-    The vectors of a tile stay in registers and LDS, so the counted traffic is
-    a small part of the sweeps: the launch is bound by the latency of its
-    dependent team synchronisations, not by HBM."""
+SWEEP_BASIS = "algorithmic sweep bytes (23 + 9 n_cg) x 4 B per pixel per GN iteration / launch time"
+IO_BASIS = "inputs read once and outputs written once, 10 x 4 B per pixel / launch time"
+
+
+def roofline_entry(kernel, bpl, launch_s, traffic, sync=None, basis=SWEEP_BASIS):
+    """The solver's roofline figures: algorithmic bytes per launch / launch time
+    against HBM peak (achieved, frac), the HBM bytes rocprofv3 counted per launch
+    (traffic) and the rate they give, and the team-synchronisation figures. The
+    algorithmic bytes are the sweeps that PCG of one iteration at a time would
+    make, or, for s-step PCG, which has no such sweeps, what it cannot do without.
+    The vectors of a tile stay in registers and LDS: the launch is bound by the
+    latency of its dependent team synchronisations, not by HBM."""
     achieved = bpl / launch_s / 1e9
     out = {"kernel": kernel, "bound": "latency", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-           "achieved_basis": "algorithmic sweep bytes (23 + 9 n_cg) x 4 B per pixel per GN iteration / launch time",
+           "achieved_basis": basis,
            "algorithmic_bytes_per_launch": bpl, "avg_launch_ms": round(launch_s * 1000.0, 4)}
     if traffic:
         out["counted_gbs"] = round(traffic / launch_s / 1e9, 2)
@@ -535,7 +558,8 @@ def run_headline(a, torch):
     kf, total1, stereo_ms, solve_ms, lat_ms = timed(False)
     solver_layout = kf.solver_layout()
     syncs = kf.stats().team_syncs
-    sync = sync_floor(kf, torch, syncs, float(np.mean(solve_ms)))
+    cg_form, kernel = solver_in_use(a.cg_variant, wl["n_gn"], wl["n_cg"], syncs)
+    sync = sync_floor(kf, torch, syncs, float(np.mean(solve_ms)), kernel)
     kf.close()
     kf, total, _, _, lat_p = timed(True)
     st = kf.stats()
@@ -544,7 +568,8 @@ def run_headline(a, torch):
     px = nF * case.W * case.H
     value = px / (ms_per_step / 1000.0) / 1e6
     N = case.W * case.H
-    bpl = solver_bytes_per_frame(N, wl["n_gn"], wl["n_cg"])
+    bpl, basis = ((solver_io_bytes(N), IO_BASIS) if kernel == "k_sstep"
+                  else (solver_bytes_per_frame(N, wl["n_gn"], wl["n_cg"]), SWEEP_BASIS))
     solve_avg_s = float(np.mean(solve_ms)) / 1000.0
     out = {
         "metric": METRIC,
@@ -568,7 +593,7 @@ def run_headline(a, torch):
             "frames_per_step": nF, "width": case.W, "height": case.H, "seed": kfsynth.seed_for(wl["config"], 0),
             "solver_layout": solver_layout, "pipeline_frames": 1,
             "solver_launch": "cooperative" if a.cooperative else "plain",
-            "cg_variant": "pipelined" if a.cg_variant in ("auto", "pipelined") else "textbook",
+            "cg_variant": cg_form,
         },
         "latency_ms": {"p50": round(float(np.percentile(lat_p, 50)), 4),
                        "p99": round(float(np.percentile(lat_p, 99)), 4),
@@ -583,7 +608,7 @@ def run_headline(a, torch):
                                "solve": round(float(np.mean(solve_ms)), 4)},
         "frame_stats": {"textured": st.n_searched, "semi_valid": st.n_valid, "scale": round(st.scale, 6),
                         "team_syncs_per_solve": syncs},
-        "roofline": roofline_entry("k_solve", bpl, solve_avg_s, load_traffic(TRAFFIC_FILE, solver_layout), sync),
+        "roofline": roofline_entry(kernel, bpl, solve_avg_s, load_traffic(TRAFFIC_FILE, solver_layout), sync, basis),
         "context": {"paper": "16 ms semi-dense + 33 ms optimisation per frame on i7-5820K + GTX 980, "
                              "resolution unstated (Table IV)"},
     }
@@ -611,17 +636,22 @@ def probe_us_per_sync(kf, torch, rounds, nvalues=2, repeats=3):
     return best
 
 
-def sync_floor(kf, torch, syncs, solve_ms, rounds=2000):
-    """Team-synchronisation floor of the solve: the probe launch (same team,
-    tiling and exchange as the solve, no arithmetic) timed with HIP events on
-    the context's stream; floor = synchronisations per solve x time per probe
-    round."""
+def sync_floor(kf, torch, syncs, solve_ms, kernel, rounds=2000):
+    """Team synchronisations of the solve against the probe launch (same team and
+    tile grid, the exchange of pipelined PCG, no arithmetic) timed with HIP events
+    on the context's stream. For k_solve, whose exchange it is, synchronisations
+    per solve x time per probe round is a floor; k_sstep's carry more values and
+    wider boundaries, and their time is given beside the probe's."""
     best = probe_us_per_sync(kf, torch, rounds)
-    floor_ms = syncs * best / 1000.0
-    return {"syncs_per_launch": syncs, "probe_us_per_sync": round(best, 4), "floor_ms": round(floor_ms, 4),
-            "frac": round(floor_ms / solve_ms, 4),
-            "probe": f"kf_probe_sync: {rounds} exchanges of 2 partials + the tile boundary, same team and tiling "
-                     "as the solve, no arithmetic; fastest of 3 launches"}
+    out = {"syncs_per_launch": syncs, "probe_us_per_sync": round(best, 4),
+           "solve_us_per_sync": round(1000.0 * solve_ms / syncs, 4)}
+    if kernel == "k_solve":
+        floor_ms = syncs * best / 1000.0
+        out.update(floor_ms=round(floor_ms, 4), frac=round(floor_ms / solve_ms, 4))
+    out["probe"] = (f"kf_probe_sync: {rounds} exchanges of 2 partials + the tile boundary, one pixel deep, same team "
+                    f"and tiles as the solve, no arithmetic; fastest of 3 launches"
+                    + ("" if kernel == "k_solve" else "; the solve's own synchronisations are others"))
+    return out
 
 
 # team shapes (tiles_x, tiles_y) of the synchronisation sweep, up to the largest

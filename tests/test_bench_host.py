@@ -33,6 +33,23 @@ def test_algorithmic_bytes_of_the_headline_solve():
     assert bench.solver_bytes_per_frame(640 * 480, 10, 20) == 10 * (23 + 180) * 4 * 640 * 480 == 2494464000
 
 
+@pytest.mark.parametrize("cg_variant,syncs,form,kernel", [
+    ("auto", 60, "s-step", "k_sstep"),         # 10 x (5 blocks of 4 and the scale step)
+    ("auto", 110, "s-step", "k_sstep"),        # blocks of 2
+    ("auto", 210, "pipelined", "k_solve"),     # an explicit workgroup size
+    ("pipelined", 210, "pipelined", "k_solve"),
+    ("textbook", 400, "textbook", "k_solve"),
+])
+def test_the_solver_that_ran_is_named(cg_variant, syncs, form, kernel):
+    assert bench.solver_in_use(cg_variant, 10, 20, syncs) == (form, kernel)
+
+
+def test_roofline_of_the_sstep_solver_counts_what_it_cannot_do_without():
+    r = bench.roofline_entry("k_sstep", bench.solver_io_bytes(640 * 480), 350e-6, None, basis=bench.IO_BASIS)
+    assert r["algorithmic_bytes_per_launch"] == 12288000 and r["achieved_basis"] == bench.IO_BASIS
+    assert r["frac"] == round(12288000 / 350e-6 / 8e12, 4)
+
+
 def test_source_hash_ignores_comments_and_blank_space(tmp_path):
     a, b, c = tmp_path / "a.hip", tmp_path / "b.hip", tmp_path / "c.hip"
     a.write_text("int f(int x) {\n  return x + 1;\n}\n")
