@@ -18,7 +18,8 @@ namespace kf {
 // Ops: Stream, Event; bool create(Event&), destroy(Event&); bool record(Event&, Stream)
 // (false: not possible now, for instance because the stream is being captured);
 // bool done(Event&); bool wait(Stream, Event&); bool same(Stream, Stream);
-// bool capturing(Stream).
+// bool capturing(Stream); bool detach(Event&): the event, recorded, no longer refers
+// to the stream that it was recorded on, which may go (false: waited for instead).
 template <class Ops>
 class Admission {
  public:
@@ -60,11 +61,12 @@ class Admission {
     return l;
   }
 
-  // The stream has to live until its last context has left.
-  void leave(Lane* l) {
+  // The stream has to live until its last context has left, with no launch in
+  // flight if `ended`.
+  void leave(Lane* l, bool ended) {
     std::lock_guard<std::mutex> lock(mu_);
     if (--l->refs > 0) return;
-    if (in_flight(l)) return;   // kept until a later launch finds it done
+    if (!ended && in_flight(l) && ops_.detach(l->event)) return;   // kept until a later launch finds it done
     remove(l);
   }
 

@@ -28,21 +28,44 @@ struct HipOps {
   using Stream = hipStream_t;
   using Event = hipEvent_t;
   int device;
-  // orders work of this device only, so without the system-scope fence
-  bool create(Event& e) const {
+  Stream own = nullptr;   // takes over events of streams that may go (detach)
+
+  template <typename F>
+  bool on_device(F&& f) const {
     int cur = -1;
     if (!good(hipGetDevice(&cur)) || (cur != device && !good(hipSetDevice(device)))) return false;
-    const bool made = good(hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventDisableSystemFence));
+    const bool ok = f();
     if (cur != device) (void)good(hipSetDevice(cur));
-    return made;
+    return ok;
+  }
+  // orders work of this device only, so without the system-scope fence
+  bool create(Event& e) const {
+    return on_device([&] { return good(hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventDisableSystemFence)); });
   }
   void destroy(Event& e) const { (void)good(hipEventDestroy(e)); }
   bool record(Event& e, Stream s) const { return !capturing(s) && good(hipEventRecord(e, s)); }
   bool done(Event& e) const {
     Relaxed relaxed;
     const hipError_t r = hipEventQuery(e);
-    if (r == hipErrorNotReady) (void)hipGetLastError();
+    if (r != hipSuccess) (void)hipGetLastError();
     return r != hipErrorNotReady;
+  }
+  // An event keeps referring to the stream that it was last recorded on: asked for
+  // after that stream is destroyed, the runtime answers at random (seen: that it was
+  // recorded in a capture). So a stream of the library's waits for it and records
+  // one of its own.
+  bool detach(Event& e) {
+    Relaxed relaxed;
+    if (!own && !on_device([&] { return good(hipStreamCreateWithFlags(&own, hipStreamNonBlocking)); })) own = nullptr;
+    Event mine = nullptr;
+    if (own && create(mine) && wait(own, e) && good(hipEventRecord(mine, own))) {
+      destroy(e);
+      e = mine;
+      return true;
+    }
+    if (mine) destroy(mine);
+    (void)good(hipEventSynchronize(e));
+    return false;
   }
   bool wait(Stream s, Event& e) const { return good(hipStreamWaitEvent(s, e, 0)); }
   // (a per-thread default stream is another one in every thread)
@@ -62,7 +85,7 @@ Device* admission_of(int device) {
   static Device* all[MAX_DEVICES] = {};
   if (device < 0 || device >= MAX_DEVICES) return nullptr;
   std::lock_guard<std::mutex> lock(mu);
-  if (!all[device]) all[device] = new (std::nothrow) Device(device_cus(device), HipOps{device});
+  if (!all[device]) all[device] = new (std::nothrow) Device(device_cus(device), HipOps{device, nullptr});
   return all[device];
 }
 
@@ -82,7 +105,8 @@ hipError_t admit_launch(kf_ctx* c, int blocks, int coresident, hipError_t (*go)(
 }
 
 void admit_leave(kf_ctx* c) {
-  if (c->lane) admission_of(c->device)->leave(static_cast<Device::Lane*>(c->lane));
+  // (a solve stream of the context's own has been waited for)
+  if (c->lane) admission_of(c->device)->leave(static_cast<Device::Lane*>(c->lane), c->solve_stream != nullptr);
   c->lane = nullptr;
 }
 

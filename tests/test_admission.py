@@ -19,28 +19,33 @@ PROGRAM = r"""
 #include <vector>
 #include "kf_admit.h"
 
-struct Mark { bool done = false; };
+struct Mark { bool done = false; struct Queue* on = nullptr; };
 struct Op { enum { WAIT, SOLVE, RECORD } kind; std::shared_ptr<Mark> mark; int blocks, per_cu; };
-struct Queue { std::vector<Op> ops; size_t head = 0; bool running = false, capturing = false; };
+struct Queue { std::vector<Op> ops; size_t head = 0; bool running = false, capturing = false, gone = false; };
 
 struct SimOps {
   using Stream = Queue*;
   using Event = std::shared_ptr<Mark>;
-  static int events, waits;
+  static int events, waits, dangling;
+  static Queue own;
+  void use(Event& e) { dangling += e->on && e->on->gone; }   // an event of a stream that is gone
   bool create(Event& e) { ++events; e = std::make_shared<Mark>(); e->done = true; return true; }
   void destroy(Event& e) { --events; e.reset(); }
   bool record(Event& e, Queue* q) {
     if (q->capturing) return false;
     e = std::make_shared<Mark>();   // a wait made before keeps the mark that it saw
+    e->on = q;
     q->ops.push_back({Op::RECORD, e, 0, 0});
     return true;
   }
-  bool done(Event& e) { return e->done; }
-  bool wait(Queue* q, Event& e) { ++waits; q->ops.push_back({Op::WAIT, e, 0, 0}); return true; }
+  bool done(Event& e) { use(e); return e->done; }
+  bool wait(Queue* q, Event& e) { use(e); ++waits; q->ops.push_back({Op::WAIT, e, 0, 0}); return true; }
+  bool detach(Event& e) { return wait(&own, e) && record(e, &own); }
   bool same(Queue* a, Queue* b) { return a == b; }
-  bool capturing(Queue* q) { return q->capturing; }
+  bool capturing(Queue* q) { dangling += q->gone; return q->capturing; }
 };
-int SimOps::events = 0, SimOps::waits = 0;
+int SimOps::events = 0, SimOps::waits = 0, SimOps::dangling = 0;
+Queue SimOps::own;
 using Adm = kf::Admission<SimOps>;
 
 int main(int argc, char** argv) {
@@ -50,32 +55,42 @@ int main(int argc, char** argv) {
   auto draw = [&](int n) { return (int)(rng() % n); };
   const int cus = 256, streams = 1 + draw(6);
   Adm adm(cus);
-  std::vector<Queue> q(streams);
+  std::vector<Queue*> q;          // every stream there ever was
+  std::vector<Queue*> live(streams);
+  for (Queue*& s : live) q.push_back(s = new Queue());
+  q.push_back(&SimOps::own);
   std::vector<Adm::Lane*> lane(streams, nullptr);
   int worst = 0, over = 0, solved = 0, stuck = 0;
   long left = 2000;
   auto solves = [&](int& n, int& least) {   // in flight on the device now
     n = 0; least = 1 << 20;
     int teams = 0;
-    for (Queue& s : q)
-      if (s.running) { ++teams; n += s.ops[s.head].blocks; least = std::min(least, s.ops[s.head].per_cu); }
+    for (Queue* s : q)
+      if (s->running) { ++teams; n += s->ops[s->head].blocks; least = std::min(least, s->ops[s->head].per_cu); }
     return teams;
   };
   while (left > 0 || stuck == 0) {
     if (left > 0 && draw(3) == 0) {   // the program enqueues
       --left;
       const int i = draw(streams);
-      if (draw(40) == 0 && (q[i].capturing || q[i].head == q[i].ops.size())) q[i].capturing = !q[i].capturing;
-      if (streams > 1 && draw(60) == 0 && lane[i]) { adm.leave(lane[i]); lane[i] = nullptr; continue; }
+      Queue& s = *live[i];
+      if (draw(40) == 0 && (s.capturing || s.head == s.ops.size())) s.capturing = !s.capturing;
+      if (streams > 1 && draw(60) == 0 && lane[i]) {   // its last context goes, and then the stream
+        adm.leave(lane[i], s.head == s.ops.size());
+        lane[i] = nullptr;
+        s.gone = true;
+        q.push_back(live[i] = new Queue());
+        continue;
+      }
       const int blocks = 1 + draw(draw(4) == 0 ? 512 : 256), per_cu = 1 + draw(6);
-      auto go = [&] { if (!q[i].capturing) q[i].ops.push_back({Op::SOLVE, nullptr, std::min(blocks, per_cu * cus), per_cu}); return 0; };
-      if (!lane[i]) lane[i] = adm.join(&q[i]);
+      auto go = [&] { if (!s.capturing) s.ops.push_back({Op::SOLVE, nullptr, std::min(blocks, per_cu * cus), per_cu}); return 0; };
+      if (!lane[i]) lane[i] = adm.join(&s);
       if (rule) { if (adm.launch(lane[i], std::min(blocks, per_cu * cus), per_cu, 0, 1, go)) return 3; }
       else go();
     } else {   // the device goes on at one stream
       bool any = false;
-      for (int k = 0, i = draw(streams); k < streams; ++k, i = (i + 1) % streams) {
-        Queue& s = q[i];
+      for (int k = 0, n = (int)q.size(), i = draw(n); k < n; ++k, i = (i + 1) % n) {
+        Queue& s = *q[i];
         if (s.head == s.ops.size()) continue;
         Op& op = s.ops[s.head];
         if (op.kind == Op::WAIT && !op.mark->done) continue;
@@ -96,11 +111,10 @@ int main(int argc, char** argv) {
     }
   }
   int unfinished = 0;
-  for (Queue& s : q) unfinished += s.head != s.ops.size();
-  for (Queue& s : q) s.capturing = false;
-  for (Adm::Lane* l : lane) if (l) adm.leave(l);
-  printf("streams %d solved %d over %d unfinished %d waits %d worst %d events %d\n", streams, solved, over, unfinished,
-         SimOps::waits, worst, SimOps::events);
+  for (Queue* s : q) unfinished += s->head != s->ops.size();
+  for (Adm::Lane* l : lane) if (l) adm.leave(l, true);
+  printf("streams %d solved %d over %d unfinished %d waits %d worst %d dangling %d\n", streams, solved, over, unfinished,
+         SimOps::waits, worst, SimOps::dangling);
   return 0;
 }
 """
@@ -128,11 +142,12 @@ def _run(program, seed, rule):
 def test_solves_on_different_streams_fit_together(program):
     """Whatever the order in which streams make progress, the solves on the device
     at one time have places for all their workgroups, and every launch comes to
-    its end; without the rule they do not fit."""
+    its end; without the rule they do not fit. No event is used after the stream
+    that it was recorded on is gone."""
     broken = 0
     for seed in range(200):
         r = _run(program, seed, True)
-        assert r["over"] == 0 and r["unfinished"] == 0, (seed, r)
+        assert r["over"] == 0 and r["unfinished"] == 0 and r["dangling"] == 0, (seed, r)
         if r["streams"] == 1:
             assert r["waits"] == 0, (seed, r)
         broken += _run(program, seed, False)["over"] > 0

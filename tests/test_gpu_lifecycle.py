@@ -204,3 +204,37 @@ def test_probe_starts_from_cleared_words(cg_variant):
         assert not (tail == np.frombuffer(b"\xa5" * 8, np.int64)[0]).any()
         assert kf.stats().team_syncs == 1
     kf.close()
+
+
+def test_contexts_come_and_go_with_solves_in_flight():
+    """Contexts on streams of their own (a frame-pipelined one with an internal
+    stream) are destroyed right after their calls, while others go on: no call
+    fails, and the last ones' results are those of the same calls alone."""
+    from paper_2207_12244_amd.kf import Keyframe
+    t = gu.torch()
+    c = kfsynth.config_case(3, 30, size_index=3, frames=2)
+    maps = [gu.dev(c.image0, t.uint8), *[gu.dev(m, t.float32) for m in c.priors.maps()]]
+    images = [gu.dev(im, t.uint8) for im in c.images]
+    streams = [t.cuda.Stream() for _ in range(3)]
+    t.cuda.synchronize()
+
+    def life(stream, pipelined):
+        kf = Keyframe(c.W, c.H, precision="f32", n_samples=32, K=c.K, stream=stream, pipeline_frames=pipelined)
+        kf.set_prior(*maps, c.T_wc0)
+        for im, T in zip(images, c.poses):
+            kf.fuse_frame(im, T)
+        return kf
+
+    alone = gu.np_state(life(t.cuda.current_stream(), False))
+    gone = []   # their workspaces stay until the device has passed the calls
+    for _ in range(12):
+        kfs = [life(s, i == 0) for i, s in enumerate(streams)]
+        for kf in kfs[:2]:
+            kf.close()
+        gone += kfs
+    for kf in gone[2::3]:
+        st = gu.np_state(kf)
+        for k in ("x", "rho", "var", "match"):
+            assert np.array_equal(alone[k], st[k]), k
+        kf.close()
+    t.cuda.synchronize()
