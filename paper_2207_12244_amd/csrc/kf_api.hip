@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <iterator>
 #include <mutex>
 #include <new>
 #include <string>
@@ -191,25 +192,36 @@ double sstep_gn_us(const Tiling& t, int n_cg) {
 
 namespace {
 
-// The best (s, rows) for one tile grid; false if none fits.
-bool sstep_grid(int W, int H, int tx, int ty, int n_cg, Tiling* t) {
-  double best = 1e300;
-  auto offer = [&](int s, int rows) {
-    Tiling c{};
-    if (!sstep_fit(W, H, tx, ty, s, rows, &c)) return;
-    const double cost = sstep_gn_us(c, n_cg);
-    if (cost < best) {
-      best = cost;
-      *t = c;
+// The best (s, rows) for one tile grid, if it is better than *best: for either s
+// the fewest rows that fit, since more cost more.
+void sstep_grid(int W, int H, int tx, int ty, int n_cg, double* best, Tiling* t) {
+#define KF_LIST(R) R,
+  static const int rows2[] = {KF_SS2_ROWS(KF_LIST)}, rows4[] = {KF_SS4_ROWS(KF_LIST)};
+#undef KF_LIST
+  Tiling c{};
+  c.tile_w = (W + tx - 1) / tx;
+  c.tile_h = (H + ty - 1) / ty;
+  c.blocks = tx * ty;
+  if ((tx - 1) * c.tile_w >= W || (ty - 1) * c.tile_h >= H) return;
+  auto offer = [&](int s, const int* rows, const int* end) {
+    const int ew = std::min(W, c.tile_w + s * std::min(2, tx - 1)), eh = std::min(H, c.tile_h + s * std::min(2, ty - 1));
+    if (2 * (ew + eh) > SS_THREADS) return;
+    const int groups = SS_THREADS / ew, need = (eh + groups - 1) / groups;
+    c.s = s;
+    for (; rows != end; ++rows) {
+      if (*rows < need) continue;
+      c.rows = *rows;
+      const double cost = sstep_gn_us(c, n_cg);
+      if (cost >= *best) return;
+      Tiling f{};
+      if (!sstep_fit(W, H, tx, ty, s, *rows, &f)) continue;
+      *best = cost;
+      *t = f;
+      return;
     }
   };
-#define KF_OFFER2(R) offer(2, R);
-#define KF_OFFER4(R) offer(4, R);
-  KF_SS2_ROWS(KF_OFFER2)
-  KF_SS4_ROWS(KF_OFFER4)
-#undef KF_OFFER2
-#undef KF_OFFER4
-  return best < 1e300;
+  offer(2, std::begin(rows2), std::end(rows2));
+  offer(4, std::begin(rows4), std::end(rows4));
 }
 
 // Configurations whose depth steps the s-step solver makes: the automatic CG
@@ -236,25 +248,13 @@ bool choose_tiling(const kf_config& c, int cus, Tiling* t) {
   if (!choose_tiling_classic(W, H, c.solver_tiles_x, c.solver_tiles_y, c.solver_threads, c.precision, t)) return false;
   if (!sstep_applies(c)) return true;
   const int base = t->threads;
-  if (c.solver_tiles_x > 0) {
-    Tiling f{};
-    if (c.solver_tiles_x * c.solver_tiles_y <= most &&
-        sstep_grid(W, H, c.solver_tiles_x, c.solver_tiles_y, c.n_cg, &f))
-      *t = f;
-    t->base_threads = base;
-    return true;
-  }
   double best = 1e300;
-  for (int tx = 1; tx <= 64 && tx <= W; ++tx)
-    for (int ty = 1; ty <= 64 && ty <= H && tx * ty <= most; ++ty) {
-      Tiling f{};
-      if (!sstep_grid(W, H, tx, ty, c.n_cg, &f)) continue;
-      const double cost = sstep_gn_us(f, c.n_cg);
-      if (cost < best) {
-        best = cost;
-        *t = f;
-      }
-    }
+  if (c.solver_tiles_x > 0) {
+    if (c.solver_tiles_x * c.solver_tiles_y <= most) sstep_grid(W, H, c.solver_tiles_x, c.solver_tiles_y, c.n_cg, &best, t);
+  } else {
+    for (int tx = 1; tx <= 64 && tx <= W; ++tx)
+      for (int ty = 1; ty <= 64 && ty <= H && tx * ty <= most; ++ty) sstep_grid(W, H, tx, ty, c.n_cg, &best, t);
+  }
   t->base_threads = base;
   return true;
 }

@@ -228,3 +228,15 @@ def test_static_array_holds_its_limit_and_little_more():
     out = subprocess.run(["nm", "-S", kf.LIB_PATH], capture_output=True, text=True, check=True).stdout
     sizes = [int(l.split()[1], 16) for l in out.splitlines() if re.search(r"\b[bB] .*7scratchE", l)]
     assert len(sizes) == 1 and (4 << 20) <= sizes[0] <= (4 << 20) + (256 << 10)
+
+
+def test_sstep_cost_grows_with_the_rows():
+    """The tile search takes the fewest rows that fit a grid: the latency model has
+    to charge more for more."""
+    kf, lib = _lib()
+    f = lib["_ZN2kf11sstep_gn_usERKNS_6TilingEi"]
+    f.restype, f.argtypes = ctypes.c_double, [ctypes.c_void_p, ctypes.c_int]
+    for s, rows in ((2, (4, 6, 8, 10, 12, 14)), (4, (1, 2, 3, 4))):
+        for blocks in (1, 2, 100, 256):
+            costs = [f(ctypes.byref(_Tiling(tile_w=40, tile_h=30, blocks=blocks, s=s, rows=r)), 20) for r in rows]
+            assert all(a < b for a, b in zip(costs, costs[1:])), (s, blocks, costs)
