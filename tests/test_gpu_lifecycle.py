@@ -238,3 +238,86 @@ def test_contexts_come_and_go_with_solves_in_flight():
             assert np.array_equal(alone[k], st[k]), k
         kf.close()
     t.cuda.synchronize()
+
+
+def _plain(c, stream, maps):
+    from paper_2207_12244_amd.kf import Keyframe
+    kf = Keyframe(c.W, c.H, precision="f32", n_samples=32, K=c.K, stream=stream)
+    kf.set_prior(*maps, c.T_wc0)
+    return kf
+
+
+def test_contexts_in_different_threads():
+    """A thread per keyframe, each on a stream of its own: the results of the same
+    calls in one thread."""
+    import threading
+    t = gu.torch()
+    cases = [kfsynth.config_case(3, 40 + i, size_index=s, frames=6) for i, s in enumerate((3, 2, 3))]
+    maps = [[gu.dev(c.image0, t.uint8), *[gu.dev(m, t.float32) for m in c.priors.maps()]] for c in cases]
+    images = [[gu.dev(im, t.uint8) for im in c.images] for c in cases]
+    t.cuda.synchronize()
+
+    def life(i, stream, out):
+        kf = _plain(cases[i], stream, maps[i])
+        for im, T in zip(images[i], cases[i].poses):
+            kf.fuse_frame(im, T)
+        out[i] = gu.np_state(kf)
+        kf.close()
+
+    alone, mixed = {}, {}
+    for i in range(3):
+        life(i, t.cuda.current_stream(), alone)
+    threads = [threading.Thread(target=life, args=(i, t.cuda.Stream(), mixed)) for i in range(3)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    for i in range(3):
+        for k in ("x", "rho", "var", "match"):
+            assert np.array_equal(alone[i][k], mixed[i][k]), (i, k)
+
+
+def test_captured_call_beside_another_stream():
+    """A captured kf_fuse_frame_static, captured and replayed while a context on
+    another stream has solves in flight: every replay is the eager call's result,
+    and the other context's results are its own."""
+    import ctypes
+    from paper_2207_12244_amd import kf as K
+    t = gu.torch()
+    lib = K.load_library()
+    c, o = kfsynth.config_case(3, 50, size_index=1, frames=1), kfsynth.config_case(3, 51, size_index=3, frames=1)
+    maps, maps_o = ([gu.dev(v.image0, t.uint8), *[gu.dev(m, t.float32) for m in v.priors.maps()]] for v in (c, o))
+    img, img_o = gu.dev(c.images[0], t.uint8), gu.dev(o.images[0], t.uint8)
+    s, so = t.cuda.Stream(), t.cuda.Stream()
+    t.cuda.synchronize()
+    eager, captured, other, other_alone = (_plain(v, st, m) for v, st, m in (
+        (c, s, maps), (c, s, maps), (o, so, maps_o), (o, so, maps_o)))
+
+    def static(kf):
+        assert lib.kf_fuse_frame_static(kf.ctx, ctypes.c_void_p(img.data_ptr()), K._pose(c.poses[0])) == K.KF_OK
+
+    t.cuda.synchronize()
+    graph = t.cuda.CUDAGraph()
+    other.fuse_frame(img_o, o.poses[0])
+    with t.cuda.graph(graph, stream=s):
+        static(captured)
+        other.solve()
+    t.cuda.synchronize()
+    for replay in range(4):
+        other.solve()
+        t.cuda.synchronize()   # what a graph replays is for the caller to order
+        with t.cuda.stream(s):
+            graph.replay()
+        t.cuda.synchronize()
+        static(eager)
+        a, b = gu.np_state(eager), gu.np_state(captured)
+        for k in ("x", "rho", "var", "match"):
+            assert np.array_equal(a[k], b[k]), (replay, k)
+        assert a["tau"] == b["tau"], replay
+    other_alone.fuse_frame(img_o, o.poses[0])
+    for _ in range(5):
+        other_alone.solve()
+    a, b = gu.np_state(other_alone), gu.np_state(other)
+    assert np.array_equal(a["x"], b["x"]) and a["tau"] == b["tau"]
+    for kf in (eager, captured, other, other_alone):
+        kf.close()
