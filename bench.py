@@ -279,9 +279,7 @@ def run_batched(a, torch, cases):
     solve_ms = [ev[k][1].elapsed_time(ev[k][2]) for k in range(steps)]
     lat_ms = [ev[k][0].elapsed_time(ev[k][2]) for k in range(steps)]
     px = sum(c.W * c.H for c in cases)
-    bpl = sum(solver_bytes_per_frame(c.W * c.H, wl["n_gn"], wl["n_cg"]) for c in cases)
     solve_avg_s = float(np.mean(solve_ms)) / 1000.0
-    achieved = bpl / solve_avg_s / 1e9
     sizes = {}
     for c in cases:
         sizes[f"{c.W}x{c.H}"] = sizes.get(f"{c.W}x{c.H}", 0) + 1
@@ -299,7 +297,8 @@ def run_batched(a, torch, cases):
                        "p99": round(float(np.percentile(lat_ms, 99)), 4)},
         "stage_ms_per_step": {"stereo": round(float(np.mean(stereo_ms)), 4),
                               "solve": round(float(np.mean(solve_ms)), 4)},
-        "roofline": roofline_entry("k_solve_batch", bpl, solve_avg_s, load_traffic(BATCH_TRAFFIC_FILE, batch.layout())),
+        "roofline": roofline_entry("k_solve_batch", px, solve_avg_s, load_traffic(BATCH_TRAFFIC_FILE, batch.layout()),
+                                   solver_bytes_per_frame(px, wl["n_gn"], wl["n_cg"])),
     }
     lay = batch.layout()
     out["roofline"]["dependent_syncs_longest_queue"] = lay["max_queue"] * members[0].stats().team_syncs
@@ -346,23 +345,22 @@ def run_plain_batched(a, torch, cases, wl, imgs, poses, batched_value):
                     "latency-optimal tiling; same frames, poses and settings as the batched form"}
 
 
-SWEEP_BASIS = "algorithmic sweep bytes (23 + 9 n_cg) x 4 B per pixel per GN iteration / launch time"
-IO_BASIS = "inputs read once and outputs written once, 10 x 4 B per pixel / launch time"
-
-
-def roofline_entry(kernel, bpl, launch_s, traffic, sync=None, basis=SWEEP_BASIS):
-    """The solver's roofline figures: algorithmic bytes per launch / launch time
-    against HBM peak (achieved, frac), the HBM bytes rocprofv3 counted per launch
-    (traffic) and the rate they give, and the team-synchronisation figures. The
-    algorithmic bytes are the sweeps that PCG of one iteration at a time would
-    make, or, for s-step PCG, which has no such sweeps, what it cannot do without.
-    The vectors of a tile stay in registers and LDS: the launch is bound by the
-    latency of its dependent team synchronisations, not by HBM."""
+def roofline_entry(kernel, N, launch_s, traffic, sweep_bytes=None, sync=None):
+    """The solver's roofline figures for N pixels: the bytes that it cannot do
+    without per launch / launch time against HBM peak (achieved, frac), the HBM
+    bytes rocprofv3 counted per launch (traffic) and the rate they give, and the
+    team-synchronisation figures. The vectors of a tile stay in registers and LDS,
+    so the sweeps over memory that PCG of one iteration at a time would make
+    (sweep_bytes, where the kernel makes such iterations) are not made: the launch
+    is bound by the latency of its dependent team synchronisations, not by HBM."""
+    bpl = solver_io_bytes(N)
     achieved = bpl / launch_s / 1e9
     out = {"kernel": kernel, "bound": "latency", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-           "achieved_basis": basis,
+           "achieved_basis": "inputs read once and outputs written once, 10 x 4 B per pixel / launch time",
            "algorithmic_bytes_per_launch": bpl, "avg_launch_ms": round(launch_s * 1000.0, 4)}
+    if sweep_bytes is not None:
+        out["sweep_bytes_per_launch"] = sweep_bytes
     if traffic:
         out["counted_gbs"] = round(traffic / launch_s / 1e9, 2)
         out["counted_frac"] = round(traffic / launch_s / 1e9 / HBM_PEAK_GBS, 4)
@@ -568,8 +566,7 @@ def run_headline(a, torch):
     px = nF * case.W * case.H
     value = px / (ms_per_step / 1000.0) / 1e6
     N = case.W * case.H
-    bpl, basis = ((solver_io_bytes(N), IO_BASIS) if kernel == "k_sstep"
-                  else (solver_bytes_per_frame(N, wl["n_gn"], wl["n_cg"]), SWEEP_BASIS))
+    sweeps = None if kernel == "k_sstep" else solver_bytes_per_frame(N, wl["n_gn"], wl["n_cg"])
     solve_avg_s = float(np.mean(solve_ms)) / 1000.0
     out = {
         "metric": METRIC,
@@ -608,7 +605,7 @@ def run_headline(a, torch):
                                "solve": round(float(np.mean(solve_ms)), 4)},
         "frame_stats": {"textured": st.n_searched, "semi_valid": st.n_valid, "scale": round(st.scale, 6),
                         "team_syncs_per_solve": syncs},
-        "roofline": roofline_entry(kernel, bpl, solve_avg_s, load_traffic(TRAFFIC_FILE, solver_layout), sync, basis),
+        "roofline": roofline_entry(kernel, N, solve_avg_s, load_traffic(TRAFFIC_FILE, solver_layout), sweeps, sync),
         "context": {"paper": "16 ms semi-dense + 33 ms optimisation per frame on i7-5820K + GTX 980, "
                              "resolution unstated (Table IV)"},
     }

@@ -44,10 +44,11 @@ def test_the_solver_that_ran_is_named(cg_variant, syncs, form, kernel):
     assert bench.solver_in_use(cg_variant, 10, 20, syncs) == (form, kernel)
 
 
-def test_roofline_of_the_sstep_solver_counts_what_it_cannot_do_without():
-    r = bench.roofline_entry("k_sstep", bench.solver_io_bytes(640 * 480), 350e-6, None, basis=bench.IO_BASIS)
-    assert r["algorithmic_bytes_per_launch"] == 12288000 and r["achieved_basis"] == bench.IO_BASIS
-    assert r["frac"] == round(12288000 / 350e-6 / 8e12, 4)
+def test_roofline_counts_what_the_solve_cannot_do_without():
+    r = bench.roofline_entry("k_sstep", 640 * 480, 350e-6, None)
+    assert r["algorithmic_bytes_per_launch"] == 12288000 and "sweep_bytes_per_launch" not in r
+    assert r["achieved"] == round(12288000 / 350e-6 / 1e9, 2) and r["frac"] == round(12288000 / 350e-6 / 8e12, 4)
+    assert bench.roofline_entry("k_solve", 640 * 480, 6e-4, None, 2494464000)["sweep_bytes_per_launch"] == 2494464000
 
 
 def test_source_hash_ignores_comments_and_blank_space(tmp_path):
