@@ -144,7 +144,7 @@ int stage_stride(int W) { return stage_stride_impl(W); }
 namespace {
 
 constexpr int SS_THREADS = 512;
-constexpr size_t SS_SMEM_MAX = 150 * 1024;   // of 160 KiB; the kernels add up to 10 KB of their own
+constexpr size_t SS_SMEM_MAX = 150 * 1024;   // of 160 KiB (the kernels have no static LDS beside it)
 
 // Whether a tile grid fits the s-step solver with `rows` pixels per thread; the
 // extended tile (the ghost frame included) is laid out column by row group over
@@ -186,7 +186,7 @@ double sstep_gn_us(const Tiling& t, int n_cg) {
     us = t.blocks == 1 ? 2.0 + 0.32 * t.rows : 2.6 + 0.42 * t.rows + 0.011 * edge + 0.7 * team;
   else
     us = (t.blocks == 1 ? 0.8 : 1.9 + 0.0045 * edge + 0.5 * team) +
-         (t.rows <= 6 ? 0.28 : 0.32) * t.rows + (t.rows > 12 ? 0.8 : 0.0);   // 14 rows spill
+         (t.rows <= 6 ? 0.28 : 0.32) * t.rows + (t.rows > 12 ? 0.8 : 0.0);   // 12 rows spill 32 registers, 14 rows 70
   return ((n_cg + t.s - 1) / t.s + 1) * us;
 }
 
@@ -809,9 +809,8 @@ kf_status kf_stereo_update(kf_ctx* c, const uint8_t* image1, const double T_wc1[
   // unit; with none in flight (the user stream waited for them all) the
   // resident grid. The s-step solver's workgroups leave no registers for the
   // update on their compute units, so it runs on the others and, mostly, after
-  // the solve: the resident grid too (640 x 480, 30 frames pipelined: 14.0 ms
-  // with one workgroup per unit, 12.8 with two, 12.3 with three, the resident
-  // number, 12.7 with six; 320 x 240: 8.1 with any)
+  // the solve: the resident grid too (640 x 480, prior, 30 frames pipelined and
+  // read-out: 12.52 ms with one workgroup per unit, 11.74 with the resident grid)
   const bool beside = c->cfg.pipeline_frames && !c->solves_waited && !c->tiling.s;
   if (e == hipSuccess) e = launch_stereo(c->cfg.precision, c->cfg.pattern, c->cfg.n_samples, a, c->cus, beside, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "kf_stereo_update");

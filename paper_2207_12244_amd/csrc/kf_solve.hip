@@ -1109,8 +1109,12 @@ __global__ __launch_bounds__(NT) void k_sync_probe(SolveArgs a, int rounds, int 
 
 namespace {
 
-// (threads, pixels per thread) combinations whose registers fit without
-// scratch spills (the ppt_max table of the host side follows these)
+// (threads, pixels per thread) combinations; the ppt_max table of the host side
+// follows these. k_solve's need no scratch (FP64 256 x 6 uses AGPRs); k_solve_batch's
+// spill at FP32 512 x 10 pipelined (16 bytes a lane: 256 registers, and 2648 us
+// against 2979 for 40 keyframes with the loops of before, which did not), at 512 x 3
+// and 512 x 4 (16 to 76, held to two workgroups per compute unit) and FP64 256 x 6
+// with the variants (48).
 #define KF_SOLVE_COMBOS                                                              \
   KF_PPT(256, 1) KF_PPT(256, 2) KF_PPT(256, 3) KF_PPT(256, 4) KF_PPT(256, 6)          \
   KF_PPT(512, 1) KF_PPT(512, 2) KF_PPT(512, 3) KF_PPT(512, 4)                         \
