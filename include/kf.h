@@ -37,12 +37,13 @@
  *     kf_last_error gives a message for the last failure on the context.
  *   - Threading: a context is externally synchronised; distinct contexts are
  *     independent (each has its own workspace), on the same or on different
- *     streams and threads of one process. The workgroups of a solve wait for each
- *     other, so solves on different streams that might not all fit on the device
- *     run one after the other: the later one's stream waits for the earlier one's.
- *     (Many keyframes at once are the batched form's case.) Not seen, and so for
- *     the caller to order: solves that a captured graph replays, that a stream
- *     has not ended when its capture begins, and those of other processes. A context's stream must outlive it.
+ *     streams and threads of one process. A context's stream must outlive it.
+ *     The workgroups of a solve wait for each other, so solves on different
+ *     streams that might not all fit on the device run one after the other: the
+ *     later one's stream waits for the earlier one's. (Many keyframes at once are
+ *     the batched form's case.) Not seen, and so for the caller to order: solves
+ *     that a captured graph replays, solves still running on a stream when its
+ *     capture begins, and those of other processes.
  */
 #ifndef KF_H
 #define KF_H
@@ -330,8 +331,9 @@ size_t kf_batch_workspace_bytes(kf_ctx* const* members, int32_t n);
 
 /* Binds n distinct contexts (1 <= n <= KF_BATCH_MAX_MEMBERS). Members must share
    precision, pattern, n_samples, the solver workgroup size (automatic: the one that
-   the pipelined form would take) and CG variant, the device and cfg->stream, and run without pipeline_frames; they may differ in
-   size, intrinsics, tiling and iteration counts. Schedules the solver teams, uploads the static tables and
+   the pipelined form would take) and CG variant, the device and cfg->stream, and
+   run without pipeline_frames; they may differ in size, intrinsics, tiling and
+   iteration counts. Schedules the solver teams, uploads the static tables and
    (use_graph) captures the graph; allocates two small pinned host buffers.
    KF_ERR_ARG if the members are incompatible or a team cannot be co-resident.
    Members must outlive the batch; they stay usable on their own between

@@ -18,8 +18,9 @@ namespace kf {
 // Ops: Stream, Event; bool create(Event&), destroy(Event&); bool record(Event&, Stream)
 // (false: not possible now, for instance because the stream is being captured);
 // bool done(Event&); bool wait(Stream, Event&); bool same(Stream, Stream);
-// bool capturing(Stream); bool detach(Event&): the event, recorded, no longer refers
-// to the stream that it was recorded on, which may go (false: waited for instead).
+// bool capturing(Stream); bool idle(Stream): nothing is enqueued there any more, as far
+// as can be asked; bool detach(Event&): the event, recorded, no longer refers to the
+// stream that it was recorded on, which may go (false: waited for instead).
 template <class Ops>
 class Admission {
  public:
@@ -66,7 +67,8 @@ class Admission {
   void leave(Lane* l, bool ended) {
     std::lock_guard<std::mutex> lock(mu_);
     if (--l->refs > 0) return;
-    if (!ended && in_flight(l) && ops_.detach(l->event)) return;   // kept until a later launch finds it done
+    if (!ended && l->state != Lane::IDLE && !ops_.idle(l->stream) && in_flight(l) && ops_.detach(l->event))
+      return;   // kept until a later launch finds it done
     remove(l);
   }
 
@@ -75,6 +77,11 @@ class Admission {
   template <class Err, class F>
   Err launch(Lane* own, int blocks, int per_cu, Err ok, Err wait_failed, F&& go) {
     std::lock_guard<std::mutex> lock(mu_);
+    // alone on the device nothing is recorded or asked: one stream pays nothing
+    bool others = false;
+    for (Lane* l = first_; l; l = l->next) others = others || (l != own && l->state != Lane::IDLE);
+    // what a graph replays is not seen here, and other streams are left alone meanwhile
+    if ((others || own->state == Lane::MARKED) && ops_.capturing(own->stream)) return go();
     int held = 0, least = per_cu;
     bool shared = false;
     for (Lane *l = first_, *next; l; l = next) {
@@ -89,8 +96,6 @@ class Admission {
         remove(l);
       }
     }
-    // alone on the device nothing is recorded or asked: one stream pays nothing
-    if (shared && ops_.capturing(own->stream)) return go();   // what a graph replays is not seen here
     for (Lane* l = first_; l && held > 0 && held + blocks > places(least); l = l->next) {
       if (l == own || l->state != Lane::MARKED) continue;
       if (!ops_.wait(own->stream, l->event)) return wait_failed;

@@ -70,6 +70,10 @@ struct HipOps {
   bool wait(Stream s, Event& e) const { return good(hipStreamWaitEvent(s, e, 0)); }
   // (a per-thread default stream is another one in every thread)
   bool same(Stream a, Stream b) const { return a == b && a != hipStreamPerThread; }
+  bool idle(Stream s) const {
+    Relaxed relaxed;
+    return !capturing(s) && good(hipStreamQuery(s));
+  }
   bool capturing(Stream s) const {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     return !good(hipStreamIsCapturing(s, &st)) || st != hipStreamCaptureStatusNone;

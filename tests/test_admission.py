@@ -40,6 +40,7 @@ struct SimOps {
   }
   bool done(Event& e) { use(e); return e->done; }
   bool wait(Queue* q, Event& e) { use(e); ++waits; q->ops.push_back({Op::WAIT, e, 0, 0}); return true; }
+  bool idle(Queue* q) { return !q->capturing && q->head == q->ops.size(); }
   bool detach(Event& e) { return wait(&own, e) && record(e, &own); }
   bool same(Queue* a, Queue* b) { return a == b; }
   bool capturing(Queue* q) { dangling += q->gone; return q->capturing; }
@@ -76,7 +77,7 @@ int main(int argc, char** argv) {
       Queue& s = *live[i];
       if (draw(40) == 0 && (s.capturing || s.head == s.ops.size())) s.capturing = !s.capturing;
       if (streams > 1 && draw(60) == 0 && lane[i]) {   // its last context goes, and then the stream
-        adm.leave(lane[i], s.head == s.ops.size());
+        adm.leave(lane[i], draw(2) && s.head == s.ops.size());
         lane[i] = nullptr;
         s.gone = true;
         q.push_back(live[i] = new Queue());
